@@ -931,6 +931,12 @@ __global__ __launch_bounds__(kBwdThreads * CPW, CPW == 1 ? 2 : 1) void bwd_dw2_k
   // DMA form: rows of instruction i of wavefront w are tile rows RPW w + 4 i
   // + [0, 4), 1 KiB of LDS at a uniform base, lane l's 16 bytes at 16 l
   // (row l / 16, physical unit l % 16): the layout the register path stores.
+  // (Buffer and not global LDS DMA: the compiler takes the latter for a flat
+  // access that also counts as an LDS operation, and then puts vmcnt(0)
+  // lgkmcnt(0) before the next use of any LDS read, which waited for these
+  // very rows in the middle of phase A.)
+  const __amdgpu_buffer_rsrc_t xrs = bwd_rsrc(X, (int)(uint32_t)(T * Nh * (DH * 2)));
+  const __amdgpu_buffer_rsrc_t yrs = bwd_rsrc(dY, (int)(uint32_t)(T * Nh * (DH * 2)));
   auto fetch_dma = [&](const int* sl4, int buf) {
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
@@ -940,13 +946,12 @@ __global__ __launch_bounds__(kBwdThreads * CPW, CPW == 1 ? 2 : 1) void bwd_dw2_k
       const int64_t t = div_by_magic(sl, kmag);
       const int j = sl - (int)t * k;
       const int64_t th = t * Nh + h;
-      const int u = swz_tr<L::NJ1>(pu, r);
+      const uint32_t src = (uint32_t)th * (DH * 2) + 16 * swz_tr<L::NJ1>(pu, r);
       uint8_t* dst = smem + S::X_OFF + buf * S::RBUF + (RPW * wave + 4 * i) * S::TROW;
-      __builtin_amdgcn_global_load_lds(X + th * DH + 8 * u,
-                                        (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
-      __builtin_amdgcn_global_load_lds(dY + th * DH + 8 * u,
-                                        (__attribute__((address_space(3))) void*)(dst + S::TILE),
-                                        16, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(
+          xrs, (__attribute__((address_space(3))) void*)dst, 16, src, 0, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(
+          yrs, (__attribute__((address_space(3))) void*)(dst + S::TILE), 16, src, 0, 0, 0);
       pg[i] = ok ? gate[th * k + j] : 0.f;
     }
   };
@@ -1501,8 +1506,9 @@ hipError_t launch_bwd_dw(const void* X, const void* dY, const float* gate,
                      (const uint16_t*)dY, gate, perm, offsets, order, (const uint16_t*)W1, w3,  \
                      (const uint16_t*)W2, T, Nh, Ne, k, dff, dW1, dW3, dW2)
   // At d_h 128, an even number of d_ff chunks goes two chunks per workgroup
-  // (8 wavefronts share the gathered slot rows), else one.
-  const int cpw = (dff / kChunk) % 2 == 0 ? 2 : 1;
+  // (8 wavefronts share the gathered slot rows), else one; the former reads
+  // the rows through 4 GiB buffers.
+  const int cpw = (dff / kChunk) % 2 == 0 && T * Nh < (int64_t(1) << 24) ? 2 : 1;
   const dim3 grid2((unsigned)(pairs8 * (dff / kChunk / cpw)));
 #define MHL_BWD_DW2(G, C)                                                                      \
   hipLaunchKernelGGL((bwd_dw2_kernel<G, C>), grid2, dim3(kBwdThreads * C), 0, s,              \
