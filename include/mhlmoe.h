@@ -461,7 +461,7 @@ mhlmoe_status mhlmoe_bias_update(const int32_t *counts, float *bias,
  * caller's stream, so the measured interval is that kernel's execution on
  * the stream it actually runs on.  Kernel names: "route_fwd", "hist",
  * "count_scan", "scatter", "ffn", "combine", "bwd_dx", "bwd_combine",
- * "bwd_dw", "router_dw", "route_bwd", "bias_update", "proj_in", "proj_out" and
+ * "dw_plan", "bwd_dw", "router_dw", "route_bwd", "bias_update", "proj_in", "proj_out" and
  * "proj_bwd" (the projection GEMMs of the latent layer).
  *
  * mhlmoe_timing_enable(on)   start (on != 0) or stop recording; records

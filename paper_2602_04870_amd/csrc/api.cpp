@@ -413,6 +413,9 @@ mhlmoe_status backward_impl(const Shape& s, const void* X, const void* R, const 
   }));
   // dW_router from the router's input (X, or R with separate routing
   // sub-tokens) by the segment-parallel kernels.
+  MHL_TRY(run_kernel("dw_plan", stream, [&] {
+    return mhl::launch_dw_plan(offsets, s.Nh, s.Ne, order, at<int32_t>(ws, L.rdw_base), stream);
+  }));
   MHL_TRY(run_kernel("bwd_dw", stream, [&] {
     return mhl::launch_bwd_dw(X, dY, gate, perm, offsets, order, W1, W3, W2, s.T, s.Nh, s.dh,
                               s.Ne, s.k, s.dff, dW1, gelu ? nullptr : dW3, dW2, stream);
@@ -586,6 +589,9 @@ mhlmoe_status mhlmoe_route_backward(const void* X, const float* W_router, const 
   MHL_TRY(run_kernel("route_bwd", stream, [&] {
     return mhl::launch_route_bwd(idx, gate, dgate, W_router, s.T, s.Nh, s.dh, s.Ne, s.k, f32, dX,
                                  dS, stream);
+  }));
+  MHL_TRY(run_kernel("dw_plan", stream, [&] {
+    return mhl::launch_dw_plan(offsets, s.Nh, s.Ne, nullptr, at<int32_t>(ws, L.rdw_base), stream);
   }));
   return run_kernel("router_dw", stream, [&] {
     return mhl::launch_router_dw(X, f32, dS, perm, offsets, s.T, s.Nh, s.dh, s.Ne, s.k,

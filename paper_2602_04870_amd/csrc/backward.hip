@@ -25,11 +25,11 @@
 //                     current ones are used); each wavefront accumulates
 //                     dW1/dW3/dW2 in registers, then the four partial sums
 //                     are added in a fixed order.  Experts are
-//                     taken in decreasing order of slot count (dw_order_kernel)
+//                     taken in decreasing order of slot count (dw_plan_kernel)
 //                     so the longest workgroups start first.  For the contraction over slots
 //                     GEMM1 is taken with slots as rows, so a, b, v arrive with
 //                     one d_ff index per lane and the slot axis in registers;
-//   rdw_plan / router_dw_seg / router_dw_fix
+//   dw_plan / router_dw_seg / router_dw_fix
 //                     dW_r from the router's input rows, the expert's slots
 //                     cut into segments spread over workgroups.
 
@@ -523,48 +523,70 @@ __global__ __launch_bounds__(256) void bwd_combine_kernel(
 }
 
 // ---------------------------------------------------------------------------
-// Processing order of the (head, expert) pairs for the weight gradients:
-// a stable counting sort by floor(log2(slots + 1)), largest first.  One
-// workgroup; thread t takes the contiguous pairs [t n / 256, (t + 1) n / 256).
+// What the weight gradients need planned before they run, a workgroup each:
+//   block 0, the processing order of the (head, expert) pairs: by
+//     floor(log2(slots + 1)), largest first (a counting sort; the order within
+//     a class is whatever the LDS atomics give, and no result depends on it);
+//   block 1, seg_base[p], the router gradient's segments of the pairs before p
+//     (thread t scans a contiguous range of pairs).
+// One launch: the two are latency-bound and run side by side (as two launches
+// with the sort's prefix taken 64 lanes at a time they took 21 us together at
+// 512 pairs, 27 us at 2048).
 // ---------------------------------------------------------------------------
-constexpr int kOrderThreads = 256;
+constexpr int kPlanThreads = 1024;
 constexpr int kOrderBuckets = 32;
 
 __device__ __forceinline__ int order_bucket(int c) {
   return kOrderBuckets - 1 - (31 - __clz(c + 1));  // 0 for the largest counts
 }
 
-__global__ __launch_bounds__(kOrderThreads) void dw_order_kernel(const int32_t* __restrict__ offsets,
-                                                                 int Nh, int Ne,
-                                                                 int32_t* __restrict__ order) {
-  __shared__ int cnt[kOrderBuckets][kOrderThreads];
-  const int t = threadIdx.x;
-  const int64_t n = (int64_t)Nh * Ne;
-  const int64_t i0 = n * t / kOrderThreads, i1 = n * (t + 1) / kOrderThreads;
-  auto count_of = [&](int64_t i) {
-    const int64_t h = i / Ne, e = i - h * Ne;
-    const int32_t* o = offsets + h * (Ne + 1) + e;
-    return o[1] - o[0];
-  };
-  for (int b = 0; b < kOrderBuckets; ++b) cnt[b][t] = 0;
-  for (int64_t i = i0; i < i1; ++i) ++cnt[order_bucket(count_of(i))][t];
-  __syncthreads();
-  if (t < kWave) {
-    // exclusive prefix over (bucket, thread) in bucket-major order
-    int run = 0;
-    for (int b = 0; b < kOrderBuckets; ++b) {
-      for (int q = 0; q < kOrderThreads; q += kWave) {
-        const int v = cnt[b][q + t];
-        const int inc = wave_inclusive_scan(v);
-        cnt[b][q + t] = run + inc - v;
-        run += __shfl(inc, kWave - 1, kWave);
-      }
+__device__ inline int pair_slots(const int32_t* offsets, int Ne, int p) {
+  const int h = p / Ne;
+  const int32_t* o = offsets + p + h;  // h (Ne + 1) + e with p = h Ne + e
+  return o[1] - o[0];
+}
+
+__device__ inline int rdw_segments(int slots) {
+  return slots > kRdwSeg ? (slots + kRdwSeg - 1) / kRdwSeg : 1;
+}
+
+__global__ __launch_bounds__(kPlanThreads) void dw_plan_kernel(const int32_t* __restrict__ offsets,
+                                                               int Nh, int Ne,
+                                                               int32_t* __restrict__ order,
+                                                               int32_t* __restrict__ seg_base) {
+  __shared__ int cnt[kOrderBuckets];
+  __shared__ int wsum[kPlanThreads / kWave];
+  const int t = threadIdx.x, lane = t & (kWave - 1), wave = t / kWave;
+  const int P = Nh * Ne;
+  if (blockIdx.x == 0) {
+    if (order == nullptr) return;
+    if (t < kOrderBuckets) cnt[t] = 0;
+    __syncthreads();
+    for (int p = t; p < P; p += kPlanThreads) atomicAdd(&cnt[order_bucket(pair_slots(offsets, Ne, p))], 1);
+    __syncthreads();
+    if (t < kWave) {
+      const int v = t < kOrderBuckets ? cnt[t] : 0;
+      const int inc = wave_inclusive_scan(v);
+      if (t < kOrderBuckets) cnt[t] = inc - v;
     }
+    __syncthreads();
+    for (int p = t; p < P; p += kPlanThreads)
+      order[atomicAdd(&cnt[order_bucket(pair_slots(offsets, Ne, p))], 1)] = p;
+    return;
   }
+  const int lo = (int)((int64_t)P * t / kPlanThreads), hi = (int)((int64_t)P * (t + 1) / kPlanThreads);
+  int local = 0;
+  for (int p = lo; p < hi; ++p) local += rdw_segments(pair_slots(offsets, Ne, p));
+  const int inc = wave_inclusive_scan(local);
+  if (lane == kWave - 1) wsum[wave] = inc;
   __syncthreads();
-  int pos[kOrderBuckets];
-  for (int b = 0; b < kOrderBuckets; ++b) pos[b] = cnt[b][t];
-  for (int64_t i = i0; i < i1; ++i) order[pos[order_bucket(count_of(i))]++] = (int32_t)i;
+  int run = inc - local;
+  for (int w = 0; w < wave; ++w) run += wsum[w];
+  for (int p = lo; p < hi; ++p) {
+    seg_base[p] = run;
+    run += rdw_segments(pair_slots(offsets, Ne, p));
+  }
+  if (t == kPlanThreads - 1) seg_base[P] = run;
 }
 
 // ---------------------------------------------------------------------------
@@ -871,6 +893,12 @@ __device__ __forceinline__ f32x4 mfma16_bf16(bf16x8 a, bf16x8 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
+// Buffer over bytes (< 4 GiB) of token rows.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t row_buffer(const uint16_t* rows, int64_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(rows), 0, (int)(uint32_t)bytes,
+                                           0x00020000);
+}
+
 template <bool GELU, int CPW>
 __global__ __launch_bounds__(kBwdThreads * CPW, CPW == 1 ? 2 : 1) void bwd_dw2_kernel(
     const uint16_t* __restrict__ X, const uint16_t* __restrict__ dY,
@@ -932,11 +960,10 @@ __global__ __launch_bounds__(kBwdThreads * CPW, CPW == 1 ? 2 : 1) void bwd_dw2_k
   // + [0, 4), 1 KiB of LDS at a uniform base, lane l's 16 bytes at 16 l
   // (row l / 16, physical unit l % 16): the layout the register path stores.
   // (Buffer and not global LDS DMA: the compiler takes the latter for a flat
-  // access that also counts as an LDS operation, and then puts vmcnt(0)
-  // lgkmcnt(0) before the next use of any LDS read, which waited for these
-  // very rows in the middle of phase A.)
-  const __amdgpu_buffer_rsrc_t xrs = bwd_rsrc(X, (int)(uint32_t)(T * Nh * (DH * 2)));
-  const __amdgpu_buffer_rsrc_t yrs = bwd_rsrc(dY, (int)(uint32_t)(T * Nh * (DH * 2)));
+  // access that also counts as an LDS operation, and turned every wait for a
+  // fragment into lgkmcnt(0), the reads two K steps ahead included.)
+  const __amdgpu_buffer_rsrc_t xrs = row_buffer(X, T * Nh * (DH * 2));
+  const __amdgpu_buffer_rsrc_t yrs = row_buffer(dY, T * Nh * (DH * 2));
   auto fetch_dma = [&](const int* sl4, int buf) {
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
@@ -1184,8 +1211,7 @@ __global__ __launch_bounds__(kBwdThreads * CPW, CPW == 1 ? 2 : 1) void bwd_dw2_k
 // cut into segments of at most kRdwSeg rows (at least one per pair, so an
 // expert without slots gets its zeros), one workgroup per segment, so a hot
 // expert's rows spread over many workgroups:
-//   rdw_plan_kernel: seg_base[p] = segments of the pairs before p (one
-//     workgroup; thread t scans a contiguous range of pairs);
+//   dw_plan_kernel: seg_base[p] = segments of the pairs before p;
 //   router_dw_seg_kernel: a segment's sum (thread (q, part) takes rows q,
 //     q + Q, ... over 8 columns, U rows in flight, then the Q partials in q
 //     order); a one-segment pair's row goes straight to dW_router, a longer
@@ -1193,36 +1219,6 @@ __global__ __launch_bounds__(kBwdThreads * CPW, CPW == 1 ? 2 : 1) void bwd_dw2_k
 //   router_dw_fix_kernel: a longer pair's partials added in segment order.
 // Every sum has a fixed order, so the result is deterministic.
 // ---------------------------------------------------------------------------
-__device__ inline int rdw_segments(const int32_t* offsets, int Ne, int p) {
-  const int h = p / Ne, e = p - h * Ne;
-  const int c = offsets[(int64_t)h * (Ne + 1) + e + 1] - offsets[(int64_t)h * (Ne + 1) + e];
-  return c > kRdwSeg ? (c + kRdwSeg - 1) / kRdwSeg : 1;
-}
-
-__global__ __launch_bounds__(256) void rdw_plan_kernel(const int32_t* __restrict__ offsets,
-                                                       int Nh, int Ne,
-                                                       int32_t* __restrict__ seg_base) {
-  __shared__ int32_t sums[256];
-  const int P = Nh * Ne, t = threadIdx.x;
-  const int lo = (int)((int64_t)P * t / 256), hi = (int)((int64_t)P * (t + 1) / 256);
-  int local = 0;
-  for (int p = lo; p < hi; ++p) local += rdw_segments(offsets, Ne, p);
-  sums[t] = local;
-  __syncthreads();
-  for (int off = 1; off < 256; off <<= 1) {  // inclusive scan of the 256 partial sums
-    const int v = t >= off ? sums[t - off] : 0;
-    __syncthreads();
-    sums[t] += v;
-    __syncthreads();
-  }
-  int run = t == 0 ? 0 : sums[t - 1];
-  for (int p = lo; p < hi; ++p) {
-    seg_base[p] = run;
-    run += rdw_segments(offsets, Ne, p);
-  }
-  if (t == 255) seg_base[P] = sums[255];
-}
-
 template <int DH, bool XF32>
 __global__ __launch_bounds__(256) void router_dw_seg_kernel(
     const void* __restrict__ Rv, const float* __restrict__ dS,
@@ -1463,11 +1459,17 @@ hipError_t launch_bwd_combine(const int32_t* idx, const float* gate, const float
   return hipGetLastError();
 }
 
+hipError_t launch_dw_plan(const int32_t* offsets, int Nh, int Ne, int32_t* order,
+                          int32_t* seg_base, hipStream_t s) {
+  hipLaunchKernelGGL(dw_plan_kernel, dim3(2), dim3(kPlanThreads), 0, s, offsets, Nh, Ne, order,
+                     seg_base);
+  return hipGetLastError();
+}
+
 hipError_t launch_router_dw(const void* R, bool f32, const float* dS, const int32_t* perm,
                             const int32_t* offsets, int64_t T, int Nh, int dh, int Ne, int k,
-                            int32_t* seg_base, float* part, float* dWr, hipStream_t s) {
+                            const int32_t* seg_base, float* part, float* dWr, hipStream_t s) {
   const int P = Nh * Ne;
-  hipLaunchKernelGGL(rdw_plan_kernel, dim3(1), dim3(256), 0, s, offsets, Nh, Ne, seg_base);
   const dim3 grid((unsigned)rdw_max_segments(T, Nh, Ne, k));
 #define MHL_RDW(DH, F)                                                                         \
   do {                                                                                         \
@@ -1491,11 +1493,10 @@ hipError_t launch_router_dw(const void* R, bool f32, const float* dS, const int3
 }
 
 hipError_t launch_bwd_dw(const void* X, const void* dY, const float* gate,
-                         const int32_t* perm, const int32_t* offsets, int32_t* order,
+                         const int32_t* perm, const int32_t* offsets, const int32_t* order,
                          const void* W1, const void* W3, const void* W2, int64_t T, int Nh,
                          int dh, int Ne, int k, int dff, float* dW1, float* dW3, float* dW2,
                          hipStream_t s) {
-  hipLaunchKernelGGL(dw_order_kernel, dim3(1), dim3(kOrderThreads), 0, s, offsets, Nh, Ne, order);
   const int64_t pairs8 = ((int64_t)Nh * Ne + kXcds - 1) / kXcds * kXcds;
   const dim3 grid((unsigned)(pairs8 * (dff / kChunk)));
   // W3 == NULL: the GELU expert (W3 never read, dW3 never written).

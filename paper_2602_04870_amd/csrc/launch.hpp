@@ -163,28 +163,32 @@ hipError_t launch_bwd_combine(const int32_t* idx, const float* gate, const float
                               int dh, int Ne, int k, void* dX, void* dR, float* dS,
                               hipStream_t s);
 
+// From the clustering's offsets: order (Nh * Ne ints, or NULL), the (head,
+// expert) processing order of launch_bwd_dw, experts with the most slots
+// first, and seg_base (Nh * Ne + 1 ints), the segments of launch_router_dw.
+hipError_t launch_dw_plan(const int32_t* offsets, int Nh, int Ne, int32_t* order,
+                          int32_t* seg_base, hipStream_t s);
+
 // Backward, step 3: dW1, dW3 and dW2 of every (head, expert), written in
-// full (zeros where the expert received no slot).  order (Nh * Ne ints of
-// workspace) receives the (head, expert) processing order, experts with the
-// most slots first.  W3 == NULL: the GELU expert (dW1 = dW_in, dW2 = dW_out;
+// full (zeros where the expert received no slot), in launch_dw_plan's order.  W3 == NULL: the GELU expert (dW1 = dW_in, dW2 = dW_out;
 // dW3 not written).
 hipError_t launch_bwd_dw(const void* X, const void* dY, const float* gate,
-                         const int32_t* perm, const int32_t* offsets, int32_t* order,
+                         const int32_t* perm, const int32_t* offsets, const int32_t* order,
                          const void* W1, const void* W3, const void* W2, int64_t T, int Nh,
                          int dh, int Ne, int k, int dff, float* dW1, float* dW3, float* dW2,
                          hipStream_t s);
 
 // dW_router[h][e] = sum over e's slots of dS_slot R[t][h] (bf16 R, fp32 when
 // f32), every (head, expert) written.  Each pair's rows are cut into segments of at most
-// kRdwSeg rows; seg_base (Nh * Ne + 1 ints) and part
-// (rdw_max_segments * dh floats) are workspace.
+// kRdwSeg rows (seg_base: launch_dw_plan's); part (rdw_max_segments * dh
+// floats) is workspace.
 constexpr int kRdwSeg = 1024;
 __host__ __device__ inline int64_t rdw_max_segments(int64_t T, int Nh, int Ne, int k) {
   return (int64_t)Nh * Ne + ceil_div((int64_t)Nh * T * k, kRdwSeg);
 }
 hipError_t launch_router_dw(const void* R, bool f32, const float* dS, const int32_t* perm,
                             const int32_t* offsets, int64_t T, int Nh, int dh, int Ne, int k,
-                            int32_t* seg_base, float* part, float* dWr, hipStream_t s);
+                            const int32_t* seg_base, float* part, float* dWr, hipStream_t s);
 
 // Algorithm 2 from the gate gradient: dS[T][Nh][k] and
 // dX[t][h] = sum_j dS_j W_r[h, e_j] (dtype bf16, or fp32 when f32).
