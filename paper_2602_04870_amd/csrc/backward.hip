@@ -233,24 +233,17 @@ struct BwdDma {
 
   // r1, r3, r2: buffer resources over the expert's W1, W3, W2 (wave: the
   // wavefront's index, uniform).
-  __device__ __forceinline__ void issue(uint8_t* stage, __amdgpu_buffer_rsrc_t r1,
-                                        __amdgpu_buffer_rsrc_t r3, __amdgpu_buffer_rsrc_t r2,
-                                        int wave, int f0) const {
+  __device__ __forceinline__ void issue(uint8_t* stage, const u32x4& r1, const u32x4& r3,
+                                        const u32x4& r2, int wave, int f0) const {
 #pragma unroll
     for (int d = 0; d < DPW; ++d) {
       const int m = kBwdWaves * d / IPM;
       if (GELU && m == 1) continue;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(
-          m == 0 ? r1 : (m == 1 ? r3 : r2),
-          (__attribute__((address_space(3))) void*)(stage + 1024 * (kBwdWaves * d + wave)), 16,
-          voff[d], m < 2 ? f0 * DH * 2 : f0 * 2, 0, 0);
+      dma_lds16(m == 0 ? r1 : (m == 1 ? r3 : r2), stage + 1024 * (kBwdWaves * d + wave), voff[d],
+                m < 2 ? f0 * DH * 2 : f0 * 2);
     }
   }
 };
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t bwd_rsrc(const uint16_t* base, int num_bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(base), 0, num_bytes, 0x00020000);
-}
 
 // ---------------------------------------------------------------------------
 // dX_expert and dg per slot.
@@ -282,12 +275,11 @@ __global__ __launch_bounds__(kBwdThreads, 2) void bwd_dx_kernel(
   const int wbytes = dff * DH * 2;  // one expert's W1, W3 or W2
   BwdDma<DH, GELU> dma;
   dma.init(wave, lane, dff);
-  auto rsrcs = [&](const TileInfo& t, __amdgpu_buffer_rsrc_t& r1, __amdgpu_buffer_rsrc_t& r3,
-                   __amdgpu_buffer_rsrc_t& r2) {
+  auto rsrcs = [&](const TileInfo& t, u32x4& r1, u32x4& r3, u32x4& r2) {
     const int64_t eo = ((int64_t)t.head * Ne + t.expert) * dff * DH;
-    r1 = bwd_rsrc(W1 + eo, wbytes);
-    r3 = bwd_rsrc(W3 + eo, wbytes);
-    r2 = bwd_rsrc(W2 + eo, wbytes);
+    r1 = buffer_words(W1 + eo, wbytes);
+    r3 = buffer_words(W3 + eo, wbytes);
+    r2 = buffer_words(W2 + eo, wbytes);
   };
 
   // Chunk ch of a tile sits in stage (s0 + ch) % 3 of a three-stage ring:
@@ -307,7 +299,7 @@ __global__ __launch_bounds__(kBwdThreads, 2) void bwd_dx_kernel(
   };
   int s0 = 0;
   TileInfo ti{};
-  __amdgpu_buffer_rsrc_t r1, r3, r2;
+  u32x4 r1, r3, r2;
   int tile = next_item((int)((int64_t)ntot * xcd / kXcds) + (int)(blockIdx.x / kXcds), ti);
   if (tile < t_hi) rsrcs(ti, r1, r3, r2);
   for (int tnext; tile < t_hi; tile = tnext) {
@@ -327,15 +319,13 @@ __global__ __launch_bounds__(kBwdThreads, 2) void bwd_dx_kernel(
     const float gs = ok ? gate[th * k + j] : 0.f;
     // the next tile's descriptor, read ahead
     TileInfo tn{};
-    __amdgpu_buffer_rsrc_t n1, n3, n2;
+    u32x4 n1, n3, n2;
     tnext = next_item(tile + nper, tn);
     if (tnext < t_hi) rsrcs(tn, n1, n3, n2);
-    if (nc > 1) {
-      dma.issue(smem + (s0 == 2 ? 0 : s0 + 1) * STAGE, r1, r3, r2, wave, kChunk);
-      barrier_vm<BwdDma<DH, GELU>::ISSUED>();  // chunk 0 and the rows landed
-    } else {
-      barrier_vm<0>();
-    }
+    barrier_vm<0>();  // chunk 0 and the rows landed
+    // (chunk 1 after the rows: ahead of them it made them wait, 2% where most
+    // tiles hold a few slots)
+    if (nc > 1) dma.issue(smem + (s0 == 2 ? 0 : s0 + 1) * STAGE, r1, r3, r2, wave, kChunk);
 
     f32x16 dx[DH / 32];
 #pragma unroll

@@ -112,6 +112,34 @@ __device__ __forceinline__ void barrier_vm() {
   asm volatile("" ::: "memory");
 }
 
+// Buffer resource over num_bytes (< 4 GiB) at base, as four scalars.
+__device__ __forceinline__ u32x4 buffer_words(const void* base, uint32_t num_bytes) {
+  const uint64_t a = reinterpret_cast<uint64_t>(base);
+  return u32x4{(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a),
+               (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)(a >> 32) & 0xFFFFu)),
+               (uint32_t)__builtin_amdgcn_readfirstlane((int)num_bytes), 0x00020000u};
+}
+
+// One 16-byte memory -> LDS DMA per lane that the compiler does not track:
+// the lane's bytes at byte voff + soff of the buffer (zeros past its end)
+// land at lds + 16 * lane (lds, soff wavefront-uniform).  Tracked DMA
+// (__builtin_amdgcn_*_load_lds) makes the compiler put s_waitcnt vmcnt(0)
+// before the next ds_read_b64_tr_b16, whichever LDS bytes either touches, so a
+// prefetch issued ahead of such reads was waited for at once.  The caller's
+// barrier_vm counts cover these instructions (vmcnt counts them in order); the
+// compiler's own counts leave them out and so only wait longer.  The
+// s_nop covers the scalar writes (m0, readfirstlane results) that the buffer
+// instruction reads.
+__device__ __forceinline__ void dma_lds16(u32x4 rsrc, const void* lds, uint32_t voff, uint32_t soff) {
+  const uint32_t m0 = (uint32_t)__builtin_amdgcn_readfirstlane(
+      (int)(uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)lds);
+  asm volatile(
+      "s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+      :
+      : "s"(m0), "v"(voff), "s"(rsrc), "s"(soff)
+      : "memory");
+}
+
 // Wait until this wavefront's LDS operations are done (vector-memory
 // operations, e.g. LDS DMA, may stay in flight), then barrier the workgroup.
 __device__ __forceinline__ void barrier_lds() {
