@@ -1258,6 +1258,9 @@ hipError_t launch_ffn_gelu(const void* X, const float* gate, const int32_t* perm
                            const void* W_in, const void* W_out, int64_t T, int Nh, int dh,
                            int Ne, int k, int dff, bool f32, void* yslot, hipStream_t s) {
   if (T == 0) return hipSuccess;
+  if (ws_eligible(T, Nh, dh, Ne, k, dff, f32))
+    return launch_ffn_ws(X, perm, tile_info, head_base, W_in, nullptr, W_out, T, Nh, Ne, k, yslot,
+                         s);
   if ((dh != 64 && dh != 128) || dff < kChunk || dff % kChunk != 0) return hipErrorInvalidValue;
   // fp32, or a d_ff that the pipelined kernels do not take: the generic
   // kernel over half tiles (gate-scaled per-slot outputs)
@@ -1313,6 +1316,8 @@ hipError_t launch_ffn(const void* X, const float* gate, const int32_t* perm,
                       int64_t T, int Nh, int dh, int Ne, int k, int dff,
                       bool f32, void* yslot, hipStream_t s) {
   if (T == 0) return hipSuccess;
+  if (ws_eligible(T, Nh, dh, Ne, k, dff, f32))
+    return launch_ffn_ws(X, perm, tile_info, head_base, W1, W3, W2, T, Nh, Ne, k, yslot, s);
 #define MHL_FFN(DH, F)                                                               \
   return ffn_dispatch<DH, F>(X, gate, perm, tile_info, head_base, W1, W3, W2, T, Nh, \
                              Ne, k, dff, yslot, s)

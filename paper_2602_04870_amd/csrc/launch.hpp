@@ -35,6 +35,9 @@ constexpr int kPipeTileRows = 128;
 constexpr int kQ32Grid = 512;
 constexpr int kQ32WideGrid = 256;
 constexpr int kQ32WideMinSlots = 768;
+// The weight-stationary bf16 FFN at d_h 128, d_ff 128 (ffn_ws.hip): 64-slot
+// tiles, two workgroups per CU.
+constexpr int kWsTileRows = 64;
 // The other expert kernels take a tile in two halves of 4 wavefronts each,
 // two workgroups per CU.
 constexpr int kFfnWaves = 4;
@@ -44,10 +47,10 @@ constexpr int kMaxHeadsSupported = 1024;
 
 __host__ __device__ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 __host__ __device__ inline int64_t num_token_blocks(int64_t T) { return ceil_div(T, kTokensPerBlock); }
-// Upper bound on tiles of one head for tiles of at least kPipeTileRows rows:
+// Upper bound on tiles of one head for tiles of at least kWsTileRows rows:
 // sum_e ceil(c_e / R) <= T*k/R + N_e.
 __host__ __device__ inline int64_t max_tiles_per_head(int64_t T, int k, int Ne) {
-  return ceil_div(T * k, kPipeTileRows) + Ne;
+  return ceil_div(T * k, kWsTileRows) + Ne;
 }
 
 // Half h (0 or 1) of tile list entry item / 2, as a tile of at most
@@ -107,10 +110,30 @@ inline bool q32_wide(int64_t T, int k, int Ne) {
   return T * k >= (int64_t)kQ32WideMinSlots * Ne;
 }
 
+// Whether the weight-stationary kernel runs at d_ff 128.  It loads an
+// expert's weights into registers with nothing to hide that behind (several
+// microseconds per expert and workgroup) and then streams slots faster, so it
+// pays with long runs of slots per expert and enough of them to fill 512
+// workgroups.  FFN in us, streamed (ffn_q32_kernel) / stationary, by mean slots
+// per expert and slots in all:
+//   128, 2.1 M   518 / 521        1024, 131 k   30.5 / 26.6
+//   256, 131 k   28.7 / 32.3      2048, 262 k   47.3 / 38.1
+//   256, 1.0 M   191 / 166        1250, 320 k   52.9 / 43.2
+//   512, 262 k   44.2 / 45.5      1024, 4.2 M   688 / 520
+// (GELU: the same signs.)  The X rows and the slot list are read through
+// 4 GiB buffers.
+inline bool ws_eligible(int64_t T, int Nh, int dh, int Ne, int k, int dff, bool f32) {
+  if (!q32_eligible(T, Nh, dh, dff, f32) || dff != 128 || T * Nh >= (int64_t(1) << 24)) return false;
+  const int64_t slots = T * k * Nh;
+  return (slots >= (int64_t(1) << 19) && T * k >= 256 * (int64_t)Ne) ||
+         (slots >= (int64_t(1) << 17) && T * k >= 768 * (int64_t)Ne);
+}
+
 // Rows per tile of the compact tile list that launch_ffn expects for this
-// shape: for the bf16 kernel at d_h 128 kPipeTileRows, or kTileRows where
-// q32_wide; kTileRows for the other kernels.
+// shape: kWsTileRows where ws_eligible, else for the bf16 kernel at d_h 128
+// kPipeTileRows, or kTileRows where q32_wide; kTileRows for the other kernels.
 inline int ffn_tile_rows(int64_t T, int Nh, int dh, int Ne, int k, int dff, bool f32) {
+  if (ws_eligible(T, Nh, dh, Ne, k, dff, f32)) return kWsTileRows;
   return q32_eligible(T, Nh, dh, dff, f32) && !q32_wide(T, k, Ne) ? kPipeTileRows : kTileRows;
 }
 
@@ -133,6 +156,13 @@ hipError_t launch_ffn_gelu(const void* X, const float* gate, const int32_t* perm
                            const TileInfo* tile_info, const int32_t* head_base,
                            const void* W_in, const void* W_out, int64_t T, int Nh, int dh,
                            int Ne, int k, int dff, bool f32, void* yslot, hipStream_t s);
+
+// The weight-stationary kernel where ws_eligible (W3 == NULL: GELU); called by
+// launch_ffn and launch_ffn_gelu.
+hipError_t launch_ffn_ws(const void* X, const int32_t* perm, const TileInfo* tiles,
+                         const int32_t* head_base, const void* W1, const void* W3,
+                         const void* W2, int64_t T, int Nh, int Ne, int k, void* yslot,
+                         hipStream_t s);
 
 // Whether launch_ffn's (and launch_ffn_gelu's) per-slot outputs already
 // carry the gate: false where the bf16 d_h-128 kernel runs.

@@ -1,0 +1,84 @@
+"""The weight-stationary expert FFN (bf16, d_h 128, d_ff 128, many slots per
+expert) against the CPU oracle: experts whose slot counts sit at the edges of
+its 32-slot blocks and 64-slot tiles, empty experts, several experts per
+workgroup and one expert over many workgroups."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2602_04870_amd as mh
+import workloads
+from tests.gpu_util import DeviceWorkload, announce, check_rows, to_device, to_host_f64
+
+pytestmark = pytest.mark.gpu
+
+# first-choice slots of the experts 0, 1, ...; the rest of the tokens choose
+# the expert after them, and every second choice is one of the last two
+EDGE_COUNTS = [0, 1, 31, 32, 33, 63, 64, 65, 0, 96, 127, 129]
+
+
+def _edge_routing(T, n_heads, seed):
+    rng = np.random.default_rng(seed)
+    Ne = len(EDGE_COUNTS) + 3
+    idx = np.empty((T, n_heads, 2), np.int32)
+    small = np.zeros(T, bool)
+    for h in range(n_heads):
+        first = np.full(T, len(EDGE_COUNTS), np.int32)
+        order = rng.permutation(T)
+        at = 0
+        for e, c in enumerate(EDGE_COUNTS):
+            first[order[at:at + c]] = e
+            at += c
+        small[order[:at]] = True
+        idx[:, h, 0] = first
+        idx[:, h, 1] = Ne - 2 + rng.integers(0, 2, T)
+    gate = rng.random((T, n_heads, 2)) + 0.05
+    gate /= gate.sum(-1, keepdims=True)
+    return Ne, idx, gate.astype(np.float32), small
+
+
+@pytest.mark.parametrize("expert", ["swiglu", "gelu"])
+@pytest.mark.parametrize("T,n_heads", [(65537, 1), (11000, 9)])
+def test_edge_counts(T, n_heads, expert, oracle_instance):
+    Ne, idx, gate, small = _edge_routing(T, n_heads, seed=3)
+    shape = workloads.Shape(T, n_heads, 128, Ne, 2, 128, "bf16", expert=expert)
+    # the dispatch rule: at least 2^17 slots, 768 per expert on average
+    assert shape.slots >= 1 << 17 and T * 2 >= 768 * Ne
+    announce(f"stationary ffn {expert} T={T} heads={n_heads}")
+    w = workloads.generate(shape, seed=5)
+    d = DeviceWorkload(w)
+    gi, gg = to_device(idx), to_device(gate)
+
+    def run():
+        if expert == "gelu":
+            return mh.mhlmoe_experts_gelu(d.X, gi, gg, d.W1, d.W2)
+        return mh.mhlmoe_experts(d.X, gi, gg, d.W1, d.W3, d.W2)
+
+    Y, Y2 = run(), run()
+    torch.cuda.synchronize()
+    assert torch.equal(Y, Y2), "not bitwise reproducible"
+    # every token of a small expert, and a sample of the others
+    rows = np.unique(np.concatenate([np.flatnonzero(small), workloads.sample_rows(T, 200)]))
+    args = (w.exact("X", rows), idx[rows], gate[rows].astype(np.float64), w.exact("W1"))
+    if expert == "gelu":
+        want = oracle_instance.experts_gelu(*args, w.exact("W2"))
+    else:
+        want = oracle_instance.experts(*args, w.exact("W3"), w.exact("W2"))
+    check_rows(to_host_f64(Y)[rows], want, "bf16", f"stationary ffn {expert}")
+
+
+@pytest.mark.parametrize("T,n_heads,Ne,k", [(16400, 8, 8, 4), (8200, 8, 250, 8), (8200, 8, 260, 8)])
+def test_either_side_of_the_rule(T, n_heads, Ne, k, oracle_instance):
+    """Long runs, and a mean of 256 slots per expert from both sides (the
+    last goes to the streaming kernel): the same outputs to bf16 rounding."""
+    shape = workloads.Shape(T, n_heads, 128, Ne, k, 128, "bf16")
+    announce(f"stationary ffn rule T={T} heads={n_heads} Ne={Ne} k={k}")
+    w = workloads.generate(shape, seed=7)
+    idx, gate = workloads.random_routing(T, n_heads, Ne, k, seed=9, skew=0.7)
+    d = DeviceWorkload(w)
+    Y = mh.mhlmoe_experts(d.X, to_device(idx), to_device(gate), d.W1, d.W3, d.W2)
+    torch.cuda.synchronize()
+    rows = workloads.sample_rows(T, 160)
+    want = oracle_instance.experts(w.exact("X", rows), idx[rows], gate[rows].astype(np.float64),
+                                   w.exact("W1"), w.exact("W3"), w.exact("W2"))
+    check_rows(to_host_f64(Y)[rows], want, "bf16", f"stationary ffn Ne={Ne}")
