@@ -254,7 +254,7 @@ struct BwdDma {
 // 2-3 of the row (both sides free of bank conflicts).  With the 64-byte stores
 // of the results (8 bytes per lane of 32 rows before), bwd_dx's layer backward
 // at 4096 tokens / 64 experts went from 382 to 374 us, the skewed training step
-// from 17.55 to 17.18 ms, the 384-expert GELU one from 979 to 947 us.
+// from 17.55 to 17.18 ms, the 384-expert GELU one from 979 to 951 us.
 // th: the lane's row (that of lane % 32; -1: none, zeros).
 template <int DH, int BYTES>
 struct RowTurn {
