@@ -129,7 +129,8 @@ __device__ __forceinline__ u32x4 buffer_words(const void* base, uint32_t num_byt
 // barrier_vm counts cover these instructions (vmcnt counts them in order); the
 // compiler's own counts leave them out and so only wait longer.  The
 // s_nop covers the scalar writes (m0, readfirstlane results) that the buffer
-// instruction reads.
+// instruction reads.  It writes m0 without the compiler's knowledge: not for a
+// kernel that also issues tracked DMA.
 __device__ __forceinline__ void dma_lds16(u32x4 rsrc, const void* lds, uint32_t voff, uint32_t soff) {
   const uint32_t m0 = (uint32_t)__builtin_amdgcn_readfirstlane(
       (int)(uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)lds);
