@@ -179,3 +179,53 @@ def test_latent_plan_cache_turnover():
         Y = mh.mhlmoe_layer(Xt, Wr, None, W1, W3, W2, k, return_routing=False)
         torch.cuda.synchronize()
         assert torch.equal(_bits(r["out"].reshape(Y.shape)), _bits(Y)), T
+
+
+# Shapes at which the GEMM library's first choice for one projection wants
+# 48-54 MB, more than the workspace holds (proj_in, proj_out, proj_bwd).
+@pytest.mark.parametrize("T,Nh,dh,dm", [(17349, 16, 128, 1232), (13846, 16, 64, 1760)])
+def test_latent_forward_where_the_library_wants_more_workspace(T, Nh, dh, dm):
+    announce(f"latent workspace choice forward T={T} heads={Nh} d_h={dh} d_model={dm}")
+    Ne, k, dff, N = 8, 1, 32, Nh * dh
+    gen = torch.Generator(device="cuda").manual_seed(36)
+
+    def normal(shape, std):
+        return (torch.randn(shape, generator=gen, device="cuda") * std).bfloat16()
+
+    x, W_in, W_out = (normal((T, dm), 1.0), normal((2 * N, dm), dm ** -0.5),
+                      normal((dm, N), N ** -0.5))
+    r = mh.mhlmoe_latent_layer(
+        x, W_in, normal((Nh, Ne, dh), dh ** -0.5).float(), None, normal((Nh, Ne, dff, dh), dh ** -0.5),
+        normal((Nh, Ne, dff, dh), dh ** -0.5), normal((Nh, Ne, dh, dff), dff ** -0.5), W_out, Nh, k,
+        routing_tokens=True)
+    torch.cuda.synchronize()
+    rows = workloads.sample_rows(T, 200)
+    lat = to_host_f64(x)[rows] @ to_host_f64(W_in).T
+    check_rows(to_host_f64(r["X_lat"])[rows], lat[:, :N].reshape(-1, Nh, dh), "bf16", "X_lat")
+    check_rows(to_host_f64(r["R_lat"])[rows], lat[:, N:].reshape(-1, Nh, dh), "bf16", "R_lat")
+    Y = to_host_f64(r["Y_lat"])[rows].reshape(-1, N)
+    check_rows(to_host_f64(r["out"])[rows], Y @ to_host_f64(W_out).T, "bf16", "out")
+
+
+def test_latent_backward_where_the_library_wants_more_workspace(oracle_instance):
+    T, Nh, dh, dm, Ne, k, dff = 14851, 2, 64, 1576, 8, 1, 32
+    announce(f"latent workspace choice backward T={T} heads={Nh} d_h={dh} d_model={dm}")
+    s = workloads.Shape(T, Nh, dh, Ne, k, dff, "bf16", backward=True)
+    w = workloads.generate(s, 37)
+    li = workloads.latent_inputs(s, dm, True, 37)
+    idx, gate = workloads.random_routing(T, Nh, Ne, k, seed=137)
+    dev = {n: to_device(v) for n, v in li.items()}
+    g = mh.mhlmoe_latent_layer_backward(
+        dev["x"], dev["W_in"], to_device(w.W_router), to_device(w.W1), to_device(w.W3),
+        to_device(w.W2), dev["W_out"], dev["X_lat"], dev["R_lat"], dev["Y_lat"], to_device(idx),
+        to_device(gate), dev["dout"], routing_tokens=True)
+    torch.cuda.synchronize()
+    rows = workloads.sample_rows(T, 200)  # a token's dx depends on that token only
+    want = oracle_instance.latent_layer_backward(
+        _exact(li["x"])[rows], _exact(li["W_in"]), w.exact("W_router"), w.exact("W1"),
+        w.exact("W3"), w.exact("W2"), _exact(li["W_out"]), _exact(li["X_lat"])[rows],
+        _exact(li["R_lat"])[rows], _exact(li["Y_lat"])[rows], idx[rows], gate[rows],
+        _exact(li["dout"])[rows], routing_tokens=True)
+    check_rows(to_host_f64(g["dx"])[rows], want["dx"], "bf16", "latent backward dx")
+    check_rows(to_host_f64(g["dW_out"]),
+               _exact(li["dout"]).T @ _exact(li["Y_lat"]).reshape(T, Nh * dh), "bf16", "dW_out")
