@@ -970,7 +970,8 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t row_buffer(const uint16_t* row
                                            0x00020000);
 }
 
-template <bool GELU, int CPW>
+// FAR (CPW == 2): X and dY reach past a 4 GiB buffer (see bwd_dw_form).
+template <bool GELU, int CPW, bool FAR = false>
 __global__ __launch_bounds__(kBwdThreads * CPW, CPW == 1 ? 2 : 1) void bwd_dw2_kernel(
     const uint16_t* __restrict__ X, const uint16_t* __restrict__ dY,
     const float* __restrict__ gate,
@@ -1030,9 +1031,10 @@ __global__ __launch_bounds__(kBwdThreads * CPW, CPW == 1 ? 2 : 1) void bwd_dw2_k
   // DMA form: rows of instruction i of wavefront w are tile rows RPW w + 4 i
   // + [0, 4), 1 KiB of LDS at a uniform base, lane l's 16 bytes at 16 l
   // (row l / 16, physical unit l % 16): the layout the register path stores.
-  // (Buffer and not global LDS DMA: the compiler takes the latter for a flat
-  // access that also counts as an LDS operation, and turned every wait for a
-  // fragment into lgkmcnt(0), the reads two K steps ahead included.)
+  // (Buffer and not global LDS DMA where the buffers reach: the compiler takes
+  // the latter for a flat access that also counts as an LDS operation, and
+  // turned every wait for a fragment into lgkmcnt(0), the reads two K steps
+  // ahead included.)
   const __amdgpu_buffer_rsrc_t xrs = row_buffer(X, T * Nh * (DH * 2));
   const __amdgpu_buffer_rsrc_t yrs = row_buffer(dY, T * Nh * (DH * 2));
   auto fetch_dma = [&](const int* sl4, int buf) {
@@ -1044,12 +1046,21 @@ __global__ __launch_bounds__(kBwdThreads * CPW, CPW == 1 ? 2 : 1) void bwd_dw2_k
       const int64_t t = div_by_magic(sl, kmag);
       const int j = sl - (int)t * k;
       const int64_t th = t * Nh + h;
-      const uint32_t src = (uint32_t)th * (DH * 2) + 16 * swz_tr<L::NJ1>(pu, r);
+      const int u = swz_tr<L::NJ1>(pu, r);
       uint8_t* dst = smem + S::X_OFF + buf * S::RBUF + (RPW * wave + 4 * i) * S::TROW;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(
-          xrs, (__attribute__((address_space(3))) void*)dst, 16, src, 0, 0, 0);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(
-          yrs, (__attribute__((address_space(3))) void*)(dst + S::TILE), 16, src, 0, 0, 0);
+      if constexpr (FAR) {
+        __builtin_amdgcn_global_load_lds(
+            X + th * DH + 8 * u, (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
+        __builtin_amdgcn_global_load_lds(
+            dY + th * DH + 8 * u, (__attribute__((address_space(3))) void*)(dst + S::TILE), 16, 0,
+            0);
+      } else {
+        const uint32_t src = (uint32_t)th * (DH * 2) + 16 * u;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(
+            xrs, (__attribute__((address_space(3))) void*)dst, 16, src, 0, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(
+            yrs, (__attribute__((address_space(3))) void*)(dst + S::TILE), 16, src, 0, 0, 0);
+      }
       pg[i] = ok ? gate[th * k + j] : 0.f;
     }
   };
@@ -1577,23 +1588,23 @@ hipError_t launch_bwd_dw(const void* X, const void* dY, const float* gate,
   hipLaunchKernelGGL((bwd_dw_kernel<DH, G>), grid, dim3(kBwdThreads), 0, s, (const uint16_t*)X, \
                      (const uint16_t*)dY, gate, perm, offsets, order, (const uint16_t*)W1, w3,  \
                      (const uint16_t*)W2, T, Nh, Ne, k, dff, dW1, dW3, dW2)
-  // At d_h 128, an even number of d_ff chunks goes two chunks per workgroup
-  // (8 wavefronts share the gathered slot rows), else one; the former reads
-  // the rows through 4 GiB buffers.
-  const int cpw = (dff / kChunk) % 2 == 0 && T * Nh < (int64_t(1) << 24) ? 2 : 1;
+  const DwForm form = bwd_dw_form(T, Nh, dff);
+  const int cpw = form == DwForm::kOneChunk ? 1 : 2;
   const dim3 grid2((unsigned)(pairs8 * (dff / kChunk / cpw)));
-#define MHL_BWD_DW2(G, C)                                                                      \
-  hipLaunchKernelGGL((bwd_dw2_kernel<G, C>), grid2, dim3(kBwdThreads * C), 0, s,              \
+#define MHL_BWD_DW2(G, C, FAR)                                                                 \
+  hipLaunchKernelGGL((bwd_dw2_kernel<G, C, FAR>), grid2, dim3(kBwdThreads * C), 0, s,         \
                      (const uint16_t*)X, (const uint16_t*)dY, gate, perm, offsets, order,       \
                      (const uint16_t*)W1, w3, (const uint16_t*)W2, T, Nh, Ne, k, dff, dW1, dW3, dW2)
-  if (dh == 128 && !gelu && cpw == 2)
-    MHL_BWD_DW2(false, 2);
-  else if (dh == 128 && !gelu)
-    MHL_BWD_DW2(false, 1);
-  else if (dh == 128 && cpw == 2)
-    MHL_BWD_DW2(true, 2);
+#define MHL_BWD_DW2_FORM(G)                                  \
+  do {                                                       \
+    if (form == DwForm::kOneChunk) MHL_BWD_DW2(G, 1, false); \
+    else if (form == DwForm::kTwoChunks) MHL_BWD_DW2(G, 2, false); \
+    else MHL_BWD_DW2(G, 2, true);                            \
+  } while (0)
+  if (dh == 128 && !gelu)
+    MHL_BWD_DW2_FORM(false);
   else if (dh == 128)
-    MHL_BWD_DW2(true, 1);
+    MHL_BWD_DW2_FORM(true);
   else if (dh == 64 && !gelu)
     MHL_BWD_DW(64, false);
   else if (dh == 64)
@@ -1601,6 +1612,7 @@ hipError_t launch_bwd_dw(const void* X, const void* dY, const float* gate,
   else
     return hipErrorInvalidValue;
 #undef MHL_BWD_DW
+#undef MHL_BWD_DW2_FORM
 #undef MHL_BWD_DW2
   return hipGetLastError();
 }

@@ -199,6 +199,17 @@ hipError_t launch_bwd_combine(const int32_t* idx, const float* gate, const float
 hipError_t launch_dw_plan(const int32_t* offsets, int Nh, int Ne, int32_t* order,
                           int32_t* seg_base, hipStream_t s);
 
+// The weight-gradient kernel's form at d_h 128: an even number of 32-wide d_ff
+// chunks goes two per workgroup (8 wavefronts share the gathered slot rows),
+// else one.  The two-chunk form reads the rows through 4 GiB buffers; batches
+// past them take 64-bit row addresses (2^24 rows, k 2, 64 experts, d_ff 128 /
+// 256: 10.4 / 19.2 ms that way, 12.2 / 22.3 ms one chunk per workgroup).
+enum class DwForm { kOneChunk, kTwoChunks, kTwoChunksFar };
+inline DwForm bwd_dw_form(int64_t T, int Nh, int dff) {
+  if ((dff / 32) % 2 != 0) return DwForm::kOneChunk;
+  return T * Nh < (int64_t(1) << 24) ? DwForm::kTwoChunks : DwForm::kTwoChunksFar;
+}
+
 // Backward, step 3: dW1, dW3 and dW2 of every (head, expert), written in
 // full (zeros where the expert received no slot), in launch_dw_plan's order.  W3 == NULL: the GELU expert (dW1 = dW_in, dW2 = dW_out;
 // dW3 not written).

@@ -1,0 +1,38 @@
+"""The host side of the dispatch rules in csrc/launch.hpp, built with g++
+(tests/dispatch_rules_check.cpp).  CPU only."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2602_04870_amd", "csrc")
+
+
+@pytest.fixture(scope="module")
+def lines(tmp_path_factory):
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("no g++")
+    exe = str(tmp_path_factory.mktemp("rules") / "dispatch_rules_check")
+    cmd = [gxx, "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", f"-I{CSRC}",
+           "-Wno-attributes", os.path.join(ROOT, "tests", "dispatch_rules_check.cpp"), "-o", exe]
+    res = subprocess.run(cmd, capture_output=True, text=True, timeout=300)
+    assert res.returncode == 0, res.stderr[-4000:]
+    res = subprocess.run([exe], capture_output=True, text=True, timeout=300)
+    assert res.returncode == 0, (res.stdout + res.stderr)[-4000:]
+    return [ln.split() for ln in res.stdout.splitlines()]
+
+
+def test_weight_gradients_take_two_chunks_at_every_batch(lines):
+    """An even number of d_ff chunks goes two per workgroup whatever the batch;
+    past a 4 GiB row buffer by 64-bit addresses."""
+    rows = [[int(v) for v in ln[1:]] for ln in lines if ln[0] == "dw"]
+    assert len(rows) == 16 * 3 * 7
+    one, two, two_far = 0, 1, 2
+    for T, Nh, dff, form in rows:
+        if dff % 64:
+            assert form == one
+        else:
+            assert form == (two if T * Nh * 256 < 1 << 32 else two_far)
