@@ -172,10 +172,13 @@ Layout make_layout(mhlmoe_op op, const Shape& s) {
     return L;
   }
   const int64_t mt = mhl::max_tiles_per_head(s.T, s.k, s.Ne);
+  // the weight-stationary FFN's second prefix and its shares of the tile list
+  const bool ws = op != MHLMOE_OP_LAYER_BACKWARD &&
+                  mhl::ws_eligible(s.T, s.Nh, s.dh, s.Ne, s.k, s.dff, s.dtype == MHLMOE_F32);
   L.offsets = bump(cur, sizeof(int32_t) * (size_t)s.Nh * (s.Ne + 1));
-  L.tile_start = bump(cur, sizeof(int32_t) * (size_t)s.Nh * (s.Ne + 1));
+  L.tile_start = bump(cur, sizeof(int32_t) * (size_t)s.Nh * (s.Ne + 1) * (ws ? 2 : 1));
   L.tile_info = bump(cur, sizeof(mhl::TileInfo) * (size_t)s.Nh * mt);
-  L.head_base = bump(cur, sizeof(int32_t) * (size_t)(s.Nh + 1));
+  L.head_base = bump(cur, sizeof(int32_t) * (size_t)(s.Nh + 1 + (ws ? mhl::kWsGrid + 1 : 0)));
   L.perm = bump(cur, sizeof(int32_t) * (size_t)s.Nh * s.slots());
   L.yslot = bump(cur, s.esize() * (size_t)s.T * s.Nh * s.k * s.dh);
   if (op == MHLMOE_OP_LAYER) {

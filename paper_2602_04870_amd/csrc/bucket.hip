@@ -62,34 +62,40 @@ __device__ __forceinline__ int32_t load_agent(const int32_t* p) {
   return __hip_atomic_load(const_cast<int32_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Exclusive offsets and tile prefix of one head from its counts cnt[0..Ne)
-// (one wavefront; each lane scans per_lane consecutive experts).
+// Exclusive offsets, tile prefix and (rk) prefix of experts with slots of one
+// head from its counts cnt[0..Ne) (one wavefront; each lane scans per_lane
+// consecutive experts).
 __device__ __forceinline__ void scan_head(const int* cnt, int Ne, int tile_rows,
-                                          int32_t* off, int32_t* ts) {
+                                          int32_t* off, int32_t* ts, int32_t* rk) {
   const int lane = lane_id();
   const int per_lane = (Ne + kWave - 1) / kWave;  // <= 16
-  int sc = 0, st = 0;
+  int sc = 0, st = 0, sr = 0;
   for (int i = 0; i < per_lane; ++i) {
     const int ee = lane * per_lane + i;
     const int cv = ee < Ne ? cnt[ee] : 0;
     sc += cv;
+    sr += cv > 0;
     st += tile_rows > 0 ? (cv + tile_rows - 1) / tile_rows : 0;
   }
   const int ic = wave_inclusive_scan(sc), it = wave_inclusive_scan(st);
-  int oc = ic - sc, ot = it - st;
+  const int ir = rk ? wave_inclusive_scan(sr) : 0;
+  int oc = ic - sc, ot = it - st, orr = ir - sr;
   for (int i = 0; i < per_lane; ++i) {
     const int ee = lane * per_lane + i;
     if (ee < Ne) {
       const int cv = cnt[ee];
       off[ee] = oc;
       if (ts) ts[ee] = ot;
+      if (rk) rk[ee] = orr;
       oc += cv;
+      orr += cv > 0;
       ot += tile_rows > 0 ? (cv + tile_rows - 1) / tile_rows : 0;
     }
   }
   if (lane == kWave - 1) {
     off[Ne] = ic;
     if (ts) ts[Ne] = it;
+    if (rk) rk[Ne] = ir;
   }
 }
 
@@ -100,7 +106,7 @@ __global__ __launch_bounds__(kBucketThreads) void count_scan_kernel(
     const int32_t* __restrict__ partial, int nblk, int Nh, int Ne, int tile_rows,
     int32_t* __restrict__ counts, int32_t* __restrict__ base_rel,
     int32_t* __restrict__ offsets, int32_t* __restrict__ tile_start,
-    uint32_t* __restrict__ ticket) {
+    int32_t* __restrict__ rank_start, uint32_t* __restrict__ ticket) {
   __shared__ int sums[kScanGroups][kScanExperts];
   __shared__ int staged[kStageInts];
   __shared__ bool is_last;
@@ -176,7 +182,8 @@ __global__ __launch_bounds__(kBucketThreads) void count_scan_kernel(
         staged[ee] = tot;
       }
       scan_head(staged, Ne, tile_rows, offsets + (int64_t)h * (Ne + 1),
-                tile_start ? tile_start + (int64_t)h * (Ne + 1) : nullptr);
+                tile_start ? tile_start + (int64_t)h * (Ne + 1) : nullptr,
+                rank_start ? rank_start + (int64_t)h * (Ne + 1) : nullptr);
     }
     return;
   }
@@ -214,7 +221,8 @@ __global__ __launch_bounds__(kBucketThreads) void count_scan_kernel(
     __syncthreads();
     for (int hh = wave; hh < nh; hh += kBucketWaves)
       scan_head(staged + hh * Ne, Ne, tile_rows, offsets + (int64_t)(h0 + hh) * (Ne + 1),
-                tile_start ? tile_start + (int64_t)(h0 + hh) * (Ne + 1) : nullptr);
+                tile_start ? tile_start + (int64_t)(h0 + hh) * (Ne + 1) : nullptr,
+                rank_start ? rank_start + (int64_t)(h0 + hh) * (Ne + 1) : nullptr);
     __syncthreads();
   }
   if (tid == 0) *ticket = 0u;
@@ -225,13 +233,13 @@ __global__ __launch_bounds__(kBucketThreads) void count_scan_kernel(
 __global__ __launch_bounds__(kBucketThreads) void scatter_kernel(
     const int32_t* __restrict__ idx, const int32_t* __restrict__ base_rel,
     const int32_t* __restrict__ offsets, const int32_t* __restrict__ tile_start,
-    int32_t* __restrict__ head_base, int64_t T, int Nh, int Ne, int k, int ebits,
-    int tile_rows, int64_t max_tiles, int32_t* __restrict__ perm,
+    const int32_t* __restrict__ rank_start, int32_t* __restrict__ head_base, int64_t T, int Nh,
+    int Ne, int k, int ebits, int tile_rows, int64_t max_tiles, int32_t* __restrict__ perm,
     TileInfo* __restrict__ tile_info) {
   __shared__ int whist[kBucketWaves][kMaxExperts];
   __shared__ int s_off[kMaxExperts + 1];
   __shared__ int s_ts[kMaxExperts + 1];
-  __shared__ int s_base;
+  __shared__ int s_base, s_all, s_rank, s_rank_all;
   const int blk = blockIdx.x, h = blockIdx.y, nblk = gridDim.x;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int32_t* off_h = offsets + (int64_t)h * (Ne + 1);
@@ -246,19 +254,32 @@ __global__ __launch_bounds__(kBucketThreads) void scatter_kernel(
     // this head's first tile: the tiles of every earlier head (wavefront 0
     // sums the per-head totals tile_start[h'][Ne]); the first token block of
     // each head publishes it for the FFN, the last head also the total
-    int before = 0, all = 0;
+    // (for the weight-stationary FFN also the experts with slots)
+    int before = 0, all = 0, rbefore = 0, rall = 0;
     for (int h2 = lane; h2 < Nh; h2 += kWave) {
       const int n2 = tile_start[(int64_t)h2 * (Ne + 1) + Ne];
       before += h2 < h ? n2 : 0;
       all += n2;
+      if (rank_start) {
+        const int r2 = rank_start[(int64_t)h2 * (Ne + 1) + Ne];
+        rbefore += h2 < h ? r2 : 0;
+        rall += r2;
+      }
     }
 #pragma unroll
     for (int d = kWave / 2; d > 0; d >>= 1) {
       before += __shfl_xor(before, d, kWave);
       all += __shfl_xor(all, d, kWave);
+      if (rank_start) {
+        rbefore += __shfl_xor(rbefore, d, kWave);
+        rall += __shfl_xor(rall, d, kWave);
+      }
     }
     if (lane == 0) {
       s_base = before;
+      s_all = all;
+      s_rank = rbefore;
+      s_rank_all = rall;
       if (blk == 0) {
         head_base[h] = before;
         if (h == Nh - 1) head_base[Nh] = all;
@@ -266,6 +287,8 @@ __global__ __launch_bounds__(kBucketThreads) void scatter_kernel(
     }
   }
   __syncthreads();
+  if (rank_start && s_all == 0 && blk == 0 && h == Nh - 1)  // no tile to start the shares
+    for (int m = tid; m <= kWsGrid; m += kBucketThreads) head_base[Nh + 1 + m] = 0;
   if (T == 0) return;  // (launched only to publish the empty tile list)
 
   const int64_t t0 = (int64_t)blk * kTokensPerBlock + wave * 32;
@@ -339,6 +362,15 @@ __global__ __launch_bounds__(kBucketThreads) void scatter_kernel(
     const int r0 = s_off[lo] + (int)(q - s_ts[lo]) * rpt;
     const int r1 = r0 + rpt < s_off[lo + 1] ? r0 + rpt : s_off[lo + 1];
     tiles_h[q] = TileInfo{lo, r0, r1, h};
+    if (rank_start) {
+      const int64_t i = s_base + q;
+      const WsShares sh = ws_shares_at(i, q == s_ts[lo],
+                                       s_rank + rank_start[(int64_t)h * (Ne + 1) + lo] + 1, s_all,
+                                       s_rank_all, ws_switch_tiles(T * Nh * k));
+      for (int m = sh.begin; m < sh.end; ++m) head_base[Nh + 1 + m] = (int)i;
+      if (i == s_all - 1)
+        for (int m = sh.end; m <= kWsGrid; ++m) head_base[Nh + 1 + m] = s_all;
+    }
   }
 }
 
@@ -398,7 +430,9 @@ hipError_t launch_count_scan(const int32_t* partial, int64_t T, int Nh, int Ne,
   const int nblk = (int)num_token_blocks(T);
   const dim3 grid((unsigned)ceil_div(Ne, kScanExperts), (unsigned)Nh);
   hipLaunchKernelGGL(count_scan_kernel, grid, dim3(kBucketThreads), 0, s, partial,
-                     nblk, Nh, Ne, tile_rows, counts, base_rel, offsets, tile_start, ticket);
+                     nblk, Nh, Ne, tile_rows, counts, base_rel, offsets, tile_start,
+                     tile_rows == kWsTileRows ? tile_start + (int64_t)Nh * (Ne + 1) : nullptr,
+                     ticket);
   return hipGetLastError();
 }
 
@@ -413,8 +447,9 @@ hipError_t launch_scatter(const int32_t* idx, const int32_t* base_rel,
   while ((1 << ebits) < Ne) ++ebits;
   const dim3 grid(T == 0 ? 1u : (unsigned)num_token_blocks(T), (unsigned)Nh);
   hipLaunchKernelGGL(scatter_kernel, grid, dim3(kBucketThreads), 0, s, idx,
-                     base_rel, offsets, tile_start, head_base, T, Nh, Ne, k, ebits,
-                     tile_rows, max_tiles, perm, tile_info);
+                     base_rel, offsets, tile_start,
+                     tile_rows == kWsTileRows ? tile_start + (int64_t)Nh * (Ne + 1) : nullptr,
+                     head_base, T, Nh, Ne, k, ebits, tile_rows, max_tiles, perm, tile_info);
   return hipGetLastError();
 }
 

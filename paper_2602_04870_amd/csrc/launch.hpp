@@ -38,6 +38,7 @@ constexpr int kQ32WideMinSlots = 768;
 // The weight-stationary bf16 FFN at d_h 128, d_ff 128 (ffn_ws.hip): 64-slot
 // tiles, two workgroups per CU.
 constexpr int kWsTileRows = 64;
+constexpr int kWsGrid = 512;
 // The other expert kernels take a tile in two halves of 4 wavefronts each,
 // two workgroups per CU.
 constexpr int kFfnWaves = 4;
@@ -64,6 +65,32 @@ __host__ __device__ inline TileInfo half_tile(const TileInfo* tiles, int item) {
   return t;
 }
 
+// How the weight-stationary FFN's tile list is cut into kWsGrid shares, a
+// contiguous one per workgroup: by cost, a tile counting 1 and the weights of
+// an expert ws_switch_tiles (a workgroup waits about 8 us for them and about 4
+// us per tile).  Cut by tiles alone, the workgroups with the cold experts of a
+// Zipf load ended last: at 2^20 slots, mean 512 per expert, the FFN took 192 us,
+// more than ffn_q32_kernel's 162; cut by cost it takes 139 (the even load there
+// 139 either way).  Below 2^19 slots a share has fewer than 16 tiles, too few to
+// weigh (2^17 slots, mean 2048: 25 us by tiles, 28 by cost).
+__host__ __device__ inline int ws_switch_tiles(int64_t slots) {
+  return slots >= (int64_t(1) << 19) ? 2 : 0;
+}
+// Tile i of ntot, of the rank-th (from 1) of the nexp experts with slots
+// (first: its first tile), is the first tile of the shares [begin, end); the
+// shares after the last tile's are empty.
+struct WsShares {
+  int begin, end;
+};
+__host__ __device__ inline WsShares ws_shares_at(int64_t i, bool first, int64_t rank, int64_t ntot,
+                                                 int64_t nexp, int switch_tiles) {
+  const int64_t total = ntot + switch_tiles * nexp;
+  const int64_t at = i + switch_tiles * rank;
+  const int64_t before = at - 1 - (first ? switch_tiles : 0);
+  return WsShares{i == 0 ? 0 : (int)(before * kWsGrid / total) + 1,
+                  (int)(at * kWsGrid / total) + 1};
+}
+
 // Routing forward (Algorithm 1): idx, gate and per-token-block expert
 // histograms partial[h][blk][e]; also zeroes *ticket (may be NULL) for the
 // clustering kernel that follows.
@@ -80,8 +107,10 @@ hipError_t launch_hist(const int32_t* idx, int64_t T, int Nh, int Ne, int k,
 // counts (always written) and, when base_rel is given, the per-block prefix
 // base_rel[h][blk][e]; when offsets is given, the exclusive offsets
 // [Nh][Ne+1] and (tile_start non-NULL) the prefix of per-expert tile counts
-// [Nh][Ne+1] for tiles of tile_rows slots.  *ticket must be zero on entry
-// when offsets is given (the preceding route or hist launch ensures it).
+// [Nh][Ne+1] for tiles of tile_rows slots; with tile_rows == kWsTileRows,
+// tile_start is followed by the prefix of experts with slots, [Nh][Ne+1] too.
+// *ticket must be zero on entry when offsets is given (the preceding route or
+// hist launch ensures it).
 hipError_t launch_count_scan(const int32_t* partial, int64_t T, int Nh, int Ne,
                              int tile_rows, int32_t* counts, int32_t* base_rel,
                              int32_t* offsets, int32_t* tile_start, uint32_t* ticket,
@@ -92,6 +121,8 @@ hipError_t launch_count_scan(const int32_t* partial, int64_t T, int Nh, int Ne,
 // tile_info[head_base[h] ...], head_base[h] = tiles of the earlier heads,
 // written with head_base[Nh] = all tiles): an expert with c slots gets
 // ceil(c / tile_rows) tiles of equal size rounded up to whole 32-row blocks.
+// With tile_rows == kWsTileRows, head_base[Nh + 1 + m] is the first tile of
+// share m (see ws_shares_at), m = 0 .. kWsGrid.
 hipError_t launch_scatter(const int32_t* idx, const int32_t* base_rel,
                           const int32_t* offsets, const int32_t* tile_start,
                           int32_t* head_base, int64_t T, int Nh, int Ne, int k,
@@ -110,23 +141,28 @@ inline bool q32_wide(int64_t T, int k, int Ne) {
   return T * k >= (int64_t)kQ32WideMinSlots * Ne;
 }
 
-// Whether the weight-stationary kernel runs at d_ff 128.  It loads an
-// expert's weights into registers with nothing to hide that behind (several
-// microseconds per expert and workgroup) and then streams slots faster, so it
-// pays with long runs of slots per expert and enough of them to fill 512
-// workgroups.  FFN in us, streamed (ffn_q32_kernel) / stationary, by mean slots
-// per expert and slots in all:
-//   128, 2.1 M   518 / 521        1024, 131 k   30.5 / 26.6
-//   256, 131 k   28.7 / 32.3      2048, 262 k   47.3 / 38.1
-//   256, 1.0 M   191 / 166        1250, 320 k   52.9 / 43.2
-//   512, 262 k   44.2 / 45.5      1024, 4.2 M   688 / 520
-// (GELU: the same signs.)  The X rows and the slot list are read through
-// 4 GiB buffers.
+// Whether the weight-stationary kernel runs at d_ff 128.  A workgroup waits
+// several microseconds for an expert's weights and then streams slots faster
+// than ffn_q32_kernel, so it pays with long runs of slots per expert and enough
+// of them for 512 workgroups.  FFN in us, streamed / stationary, at slots in
+// all and mean slots per expert, for an even load and a Zipf one (exponent 1.1;
+// 8 heads, k 8, SwiGLU; GELU wins at every one the rule takes, too):
+//   2^17   512   26.2 / 27.5   26.1 / 27.1     2^19   256   102 / 87     91 / 80
+//   2^17   768   29.7 / 25.9   30.0 / 25.9     2^19   512   79 / 70      79 / 70
+//   2^17  2048   25.8 / 24.6   25.4 / 24.6     2^20   256   194 / 164    170 / 141
+//   2^18   256   46.2 / 45.3   47.8 / 49.8     2^20  1024   158 / 128    156 / 138
+//   2^18   512   42.0 / 42.3   45.4 / 43.5     2^21   256   400 / 329    331 / 261
+//   2^18   768   44.3 / 39.3   45.6 / 38.4     2^22  1024   690 / 497    688 / 495
+// Below 2^19 slots the two are level until the streaming kernel goes over to its
+// 256-slot tiles, too few to fill the chip there (kQ32WideMinSlots, 768); from
+// 2^19 on the shares weigh the experts (ws_switch_tiles) and this kernel is
+// ahead at either load.  The X rows and the slot list are read through 4 GiB
+// buffers.
 inline bool ws_eligible(int64_t T, int Nh, int dh, int Ne, int k, int dff, bool f32) {
   if (!q32_eligible(T, Nh, dh, dff, f32) || dff != 128 || T * Nh >= (int64_t(1) << 24)) return false;
   const int64_t slots = T * k * Nh;
   return (slots >= (int64_t(1) << 19) && T * k >= 256 * (int64_t)Ne) ||
-         (slots >= (int64_t(1) << 17) && T * k >= 768 * (int64_t)Ne);
+         (slots >= (int64_t(1) << 17) && q32_wide(T, k, Ne));
 }
 
 // Rows per tile of the compact tile list that launch_ffn expects for this

@@ -36,3 +36,14 @@ def test_weight_gradients_take_two_chunks_at_every_batch(lines):
             assert form == one
         else:
             assert form == (two if T * Nh * 256 < 1 << 32 else two_far)
+
+
+def test_stationary_ffn_shares_are_equal_in_cost(lines):
+    """The cut of the weight-stationary FFN's tile list: complete and in order,
+    and no share dearer than an equal one by more than a tile and the weights
+    it starts and ends with."""
+    rows = [ln for ln in lines if ln[0] == "shares"]
+    assert len(rows) == 14
+    for _, what, ntot, nexp, sw, bad, equal, dearest in rows:
+        assert bad == "0", what
+        assert int(dearest) <= float(equal) + 1 + 2 * int(sw), (what, equal, dearest)

@@ -8,9 +8,10 @@ import torch
 
 import paper_2602_04870_amd as mh
 import workloads
-from tests.gpu_util import DeviceWorkload, announce, check_rows, to_device, to_host_f64
+from tests.gpu_util import (DeviceWorkload, announce, check_rows, needs_gpu, to_device,
+                            to_host_f64)
 
-pytestmark = pytest.mark.gpu
+pytestmark = [pytest.mark.gpu, needs_gpu]
 
 # first-choice slots of the experts 0, 1, ...; the rest of the tokens choose
 # the expert after them, and every second choice is one of the last two
@@ -82,3 +83,42 @@ def test_either_side_of_the_rule(T, n_heads, Ne, k, oracle_instance):
     want = oracle_instance.experts(w.exact("X", rows), idx[rows], gate[rows].astype(np.float64),
                                    w.exact("W1"), w.exact("W3"), w.exact("W2"))
     check_rows(to_host_f64(Y)[rows], want, "bf16", f"stationary ffn Ne={Ne}")
+
+
+@pytest.mark.parametrize("expert", ["swiglu", "gelu"])
+@pytest.mark.parametrize("load", ["collapsed", "zipf"])
+@pytest.mark.parametrize("T", [32768, 32767])
+def test_uneven_loads(T, load, expert, oracle_instance):
+    """Loads at which equal shares of the tiles are not equal work, from 2^19
+    slots on (where the shares weigh an expert's weights) and just below: most
+    experts of every head without a slot and a few with one to three, or a Zipf
+    load; tokens of the rare experts are all compared."""
+    n_heads, Ne, k = 8, 64, 2
+    shape = workloads.Shape(T, n_heads, 128, Ne, k, 128, "bf16", expert=expert)
+    announce(f"stationary ffn uneven {load} {expert} T={T}")
+    w = workloads.generate(shape, seed=19)
+    idx, gate = workloads.random_routing(T, n_heads, Ne, k, seed=21, skew=1.1)
+    rows = workloads.sample_rows(T, 120)
+    if load == "collapsed":
+        rng = np.random.default_rng(23)
+        for h in range(n_heads):
+            used = rng.permutation(Ne)[:3 + h % 2]
+            idx[:, h, 0] = used[0]
+            idx[:, h, 1] = used[1 + rng.integers(0, 2, T)]
+            rare = np.setdiff1d(np.arange(Ne), used)[:h]
+            at = rng.permutation(T)[:2 * len(rare)]
+            idx[at, h, 1] = np.repeat(rare, 2)
+            rows = np.union1d(rows, at)
+    else:
+        for h in range(n_heads):
+            c = np.bincount(idx[:, h].ravel(), minlength=Ne)
+            rows = np.union1d(rows, np.flatnonzero((idx[:, h] == c.argmin()).any(-1))[:40])
+    d = DeviceWorkload(w)
+    gi, gg = to_device(idx), to_device(gate)
+    Y = (mh.mhlmoe_experts_gelu(d.X, gi, gg, d.W1, d.W2) if expert == "gelu"
+         else mh.mhlmoe_experts(d.X, gi, gg, d.W1, d.W3, d.W2))
+    torch.cuda.synchronize()
+    args = (w.exact("X", rows), idx[rows], gate[rows].astype(np.float64), w.exact("W1"))
+    want = (oracle_instance.experts_gelu(*args, w.exact("W2")) if expert == "gelu"
+            else oracle_instance.experts(*args, w.exact("W3"), w.exact("W2")))
+    check_rows(to_host_f64(Y)[rows], want, "bf16", f"stationary ffn {load} {expert}")
