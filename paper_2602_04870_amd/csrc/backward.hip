@@ -288,9 +288,11 @@ struct RowTurn {
       for (int j = 0; j < 2; ++j)
         *reinterpret_cast<u32x4*>(st + (16 * j + (lane >> 2)) * 64 +
                                   16 * ((lane & 3) ^ ((lane >> 4) & 3))) = f.x[i + j];
+      wave_lds_order();
 #pragma unroll
       for (int j = 0; j < 2; ++j)
         f.x[i + j] = *reinterpret_cast<const u32x4*>(st + c * 64 + 16 * ((2 * j + g) ^ ((c >> 2) & 3)));
+      wave_lds_order();
     }
   }
 };
@@ -758,9 +760,7 @@ __global__ __launch_bounds__(kBwdThreads) void bwd_dw_kernel(
       *reinterpret_cast<u32x4*>(dyt + c * S::ROWB + (16 * s + 8 * g) * 2) = q.df.x[s];
     }
     if (g == 0) gsh[c] = q.gs;
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    wave_lds_order();
     if (r_next < row1) fetch(r_next, q);
 
     // a, b, v with slots as rows: lane = d_ff index c of the chunk,
@@ -843,9 +843,7 @@ __global__ __launch_bounds__(kBwdThreads) void bwd_dw_kernel(
         acc2[nb] = mfma32_bf16(yb, as_bf16x8(pgu[hh]), acc2[nb]);
       }
     }
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    wave_lds_order();
   };
 
   // Each wavefront takes every fourth group of 32 slots; the next group's

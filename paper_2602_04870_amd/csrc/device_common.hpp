@@ -141,6 +141,15 @@ __device__ __forceinline__ void dma_lds16(u32x4 rsrc, const void* lds, uint32_t 
       : "memory");
 }
 
+// Orders a wavefront's LDS accesses for the compiler where one lane reads what
+// another of its lanes wrote (or overwrites what another read): the hardware
+// runs a wavefront's LDS operations in order by itself, so no wait is needed.
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Wait until this wavefront's LDS operations are done (vector-memory
 // operations, e.g. LDS DMA, may stay in flight), then barrier the workgroup.
 __device__ __forceinline__ void barrier_lds() {

@@ -177,9 +177,11 @@ __global__ __launch_bounds__(Ws::THREADS, Ws::BLOCKS) void ffn_ws_kernel(
       for (int j = 0; j < 2; ++j)
         *reinterpret_cast<u32x4*>(st + (16 * j + (l >> 2)) * 64 + 16 * ((l & 3) ^ ((l >> 4) & 3))) =
             w[i + j];
+      wave_lds_order();
 #pragma unroll
       for (int j = 0; j < 2; ++j)
         w[i + j] = *reinterpret_cast<const u32x4*>(st + c * 64 + 16 * ((2 * j + g) ^ ((c >> 2) & 3)));
+      wave_lds_order();
     }
   };
   auto expert_off = [&](const TileInfo& t) { return ((int64_t)t.head * Ne + t.expert) * WEXP; };
