@@ -44,7 +44,9 @@ PEAK_TFLOPS = {"bf16": 2516.6, "f32": 157.3}
 MALL_BYTES = 256 << 20
 
 KERNELS = ("route_fwd", "hist", "count_scan", "scatter", "ffn", "combine", "bwd_dx",
-           "bwd_combine", "bwd_dw", "router_dw")
+           "bwd_combine", "dw_plan", "bwd_dw", "router_dw")
+# What an FFN launch is built from.
+FFN_SOURCES = ("experts.hip", "ffn_ws.hip", "ffn_common.hpp", "device_common.hpp", "launch.hpp")
 # MFMA flops per slot, in units of d_h * d_ff, that each kernel must do at the
 # least: the forward FFN's two GEMMs (W1, W3: 4; W2: 2); in the backward the
 # recomputed W1/W3 products, v = W2^T dy and dX = W1^T da + W3^T db are
@@ -120,7 +122,7 @@ def kernel_source_digest():
     import hashlib
     h = hashlib.sha256()
     csrc = os.path.join(ROOT, "paper_2602_04870_amd", "csrc")
-    for name in ("experts.hip", "ffn_common.hpp", "device_common.hpp", "launch.hpp"):
+    for name in FFN_SOURCES:
         with open(os.path.join(csrc, name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()[:16]
@@ -603,8 +605,8 @@ def sweep_steps(reps=20):
             fn()
         torch.cuda.synchronize()
         kern = {}
-        for kn in ("route_fwd", "ffn", "combine", "bwd_dx", "bwd_combine", "bwd_dw", "router_dw",
-                   "proj_in", "proj_out", "proj_bwd", "bias_update"):
+        for kn in ("route_fwd", "ffn", "combine", "bwd_dx", "bwd_combine", "dw_plan", "bwd_dw",
+                   "router_dw", "proj_in", "proj_out", "proj_bwd", "bias_update"):
             tot, n = mh.mhlmoe_timing_query(kn)
             if n:
                 kern[kn] = {"us_per_call": round(tot * 1e3 / reps, 2)}
@@ -641,7 +643,7 @@ def sweep_steps(reps=20):
         fn()
         torch.cuda.synchronize()
         kern = {}
-        for kn in ("bwd_dx", "bwd_combine", "bwd_dw", "router_dw"):
+        for kn in ("bwd_dx", "bwd_combine", "dw_plan", "bwd_dw", "router_dw"):
             tot, n = mh.mhlmoe_timing_query(kn)
             if n:
                 kern[kn] = {"us_per_call": round(tot * 1e3, 1)}
