@@ -122,3 +122,29 @@ def test_uneven_loads(T, load, expert, oracle_instance):
     want = (oracle_instance.experts_gelu(*args, w.exact("W2")) if expert == "gelu"
             else oracle_instance.experts(*args, w.exact("W3"), w.exact("W2")))
     check_rows(to_host_f64(Y)[rows], want, "bf16", f"stationary ffn {load} {expert}")
+
+
+@pytest.mark.parametrize("T,n_heads,Ne,k,expert", [
+    (16390, 8, 16, 1, "swiglu"), (11000, 4, 20, 3, "swiglu"), (9001, 3, 40, 5, "gelu"),
+    (5501, 2, 48, 12, "swiglu"), (2801, 2, 64, 24, "gelu"), (2200, 2, 64, 31, "swiglu"),
+    (33001, 8, 64, 3, "gelu"), (33001, 8, 64, 3, "swiglu")])
+def test_slot_division_and_long_runs(T, n_heads, Ne, k, expert, oracle_instance):
+    """k = 1 and values that are no power of two (the kernel divides slot ids
+    by a rounded magic number there), and 24 tiles per workgroup, three times
+    round the ring of slot lists."""
+    shape = workloads.Shape(T, n_heads, 128, Ne, k, 128, "bf16", expert=expert)
+    # the dispatch rule: at least 2^17 slots, 768 per expert on average
+    assert shape.slots >= 1 << 17 and T * k >= 768 * Ne
+    announce(f"stationary ffn {expert} T={T} heads={n_heads} Ne={Ne} k={k}")
+    w = workloads.generate(shape, seed=25)
+    idx, gate = workloads.random_routing(T, n_heads, Ne, k, seed=27, skew=0.7)
+    d = DeviceWorkload(w)
+    gi, gg = to_device(idx), to_device(gate)
+    Y = (mh.mhlmoe_experts_gelu(d.X, gi, gg, d.W1, d.W2) if expert == "gelu"
+         else mh.mhlmoe_experts(d.X, gi, gg, d.W1, d.W3, d.W2))
+    torch.cuda.synchronize()
+    rows = workloads.sample_rows(T, 160)
+    args = (w.exact("X", rows), idx[rows], gate[rows].astype(np.float64), w.exact("W1"))
+    want = (oracle_instance.experts_gelu(*args, w.exact("W2")) if expert == "gelu"
+            else oracle_instance.experts(*args, w.exact("W3"), w.exact("W2")))
+    check_rows(to_host_f64(Y)[rows], want, "bf16", f"stationary ffn k={k} {expert}")
