@@ -247,8 +247,8 @@ inline DwForm bwd_dw_form(int64_t T, int Nh, int dff) {
 }
 
 // Backward, step 3: dW1, dW3 and dW2 of every (head, expert), written in
-// full (zeros where the expert received no slot), in launch_dw_plan's order.  W3 == NULL: the GELU expert (dW1 = dW_in, dW2 = dW_out;
-// dW3 not written).
+// full (zeros where the expert received no slot), in launch_dw_plan's order.
+// W3 == NULL: the GELU expert (dW1 = dW_in, dW2 = dW_out; dW3 not written).
 hipError_t launch_bwd_dw(const void* X, const void* dY, const float* gate,
                          const int32_t* perm, const int32_t* offsets, const int32_t* order,
                          const void* W1, const void* W3, const void* W2, int64_t T, int Nh,
