@@ -171,10 +171,11 @@ Layout make_layout(mhlmoe_op op, const Shape& s) {
     L.total = cur;
     return L;
   }
-  const int64_t mt = mhl::max_tiles_per_head(s.T, s.k, s.Ne);
-  // the weight-stationary FFN's second prefix and its shares of the tile list
+  // the weight-stationary FFN's shorter tiles, its second prefix and its shares
+  // of the tile list
   const bool ws = op != MHLMOE_OP_LAYER_BACKWARD &&
                   mhl::ws_eligible(s.T, s.Nh, s.dh, s.Ne, s.k, s.dff, s.dtype == MHLMOE_F32);
+  const int64_t mt = mhl::max_tiles_per_head(s.T, s.k, s.Ne, ws ? mhl::kWsTileRows : mhl::kTileRows);
   L.offsets = bump(cur, sizeof(int32_t) * (size_t)s.Nh * (s.Ne + 1));
   L.tile_start = bump(cur, sizeof(int32_t) * (size_t)s.Nh * (s.Ne + 1) * (ws ? 2 : 1));
   L.tile_info = bump(cur, sizeof(mhl::TileInfo) * (size_t)s.Nh * mt);
@@ -270,7 +271,7 @@ mhlmoe_status run_kernel(const char* name, hipStream_t stream, F&& launch) {
 mhlmoe_status run_cluster(const Shape& s, const int32_t* idx, int32_t* counts, int32_t* offsets,
                           int32_t* perm, int tile_rows, const Layout& L, void* ws,
                           hipStream_t stream) {
-  const int64_t mt = mhl::max_tiles_per_head(s.T, s.k, s.Ne);
+  const int64_t mt = mhl::max_tiles_per_head(s.T, s.k, s.Ne, tile_rows);
   int32_t* partial = at<int32_t>(ws, L.partial);
   int32_t* base = at<int32_t>(ws, L.base);
   int32_t* tile_start = tile_rows > 0 ? at<int32_t>(ws, L.tile_start) : nullptr;

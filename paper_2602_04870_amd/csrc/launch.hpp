@@ -48,10 +48,11 @@ constexpr int kMaxHeadsSupported = 1024;
 
 __host__ __device__ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 __host__ __device__ inline int64_t num_token_blocks(int64_t T) { return ceil_div(T, kTokensPerBlock); }
-// Upper bound on tiles of one head for tiles of at least kWsTileRows rows:
-// sum_e ceil(c_e / R) <= T*k/R + N_e.
-__host__ __device__ inline int64_t max_tiles_per_head(int64_t T, int k, int Ne) {
-  return ceil_div(T * k, kWsTileRows) + Ne;
+// Upper bound on tiles of one head in a list of tile_rows-row tiles: sum_e
+// ceil(c_e / R) <= T*k/R + N_e, the same list size for all but the
+// weight-stationary FFN.
+__host__ __device__ inline int64_t max_tiles_per_head(int64_t T, int k, int Ne, int tile_rows) {
+  return ceil_div(T * k, tile_rows == kWsTileRows ? kWsTileRows : kPipeTileRows) + Ne;
 }
 
 // Half h (0 or 1) of tile list entry item / 2, as a tile of at most

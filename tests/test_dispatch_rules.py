@@ -6,6 +6,8 @@ import subprocess
 
 import pytest
 
+import paper_2602_04870_amd as mh
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2602_04870_amd", "csrc")
 
@@ -47,3 +49,18 @@ def test_stationary_ffn_shares_are_equal_in_cost(lines):
     for _, what, ntot, nexp, sw, bad, equal, dearest in rows:
         assert bad == "0", what
         assert int(dearest) <= float(equal) + 1 + 2 * int(sw), (what, equal, dearest)
+
+
+@pytest.mark.parametrize("shape,layer,backward", [
+    ((256, 4, 64, 16, 2, 128, mh.MHLMOE_F32), 552960, None),
+    ((4096, 8, 128, 64, 8, 256, mh.MHLMOE_BF16), 70433792, 70831360),
+    ((16384, 16, 128, 128, 8, 256, mh.MHLMOE_BF16), 564454400, 566568192),
+    ((16384, 16, 128, 256, 16, 128, mh.MHLMOE_BF16), None, 1133135104),
+    ((8192, 8, 128, 768, 8, 128, mh.MHLMOE_BF16), 143893504, 147350784),
+    ((3001, 5, 64, 100, 5, 96, mh.MHLMOE_BF16), 10624768, 10775808)])
+def test_workspace_of_calls_without_the_stationary_ffn(shape, layer, backward):
+    """Workspace sizes as they were before that kernel's longer tile lists
+    (None: a forward that takes it, or no backward in fp32)."""
+    for op, want in ((mh.MHLMOE_OP_LAYER, layer), (mh.MHLMOE_OP_LAYER_BACKWARD, backward)):
+        if want is not None:
+            assert mh.mhlmoe_workspace_size(op, *shape) == want
