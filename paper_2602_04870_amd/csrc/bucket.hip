@@ -62,9 +62,10 @@ __device__ __forceinline__ int32_t load_agent(const int32_t* p) {
   return __hip_atomic_load(const_cast<int32_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Exclusive offsets, tile prefix and (rk) prefix of experts with slots of one
+// Exclusive offsets, tile prefix and (RANK) prefix of experts with slots of one
 // head from its counts cnt[0..Ne) (one wavefront; each lane scans per_lane
 // consecutive experts).
+template <bool RANK>
 __device__ __forceinline__ void scan_head(const int* cnt, int Ne, int tile_rows,
                                           int32_t* off, int32_t* ts, int32_t* rk) {
   const int lane = lane_id();
@@ -74,11 +75,11 @@ __device__ __forceinline__ void scan_head(const int* cnt, int Ne, int tile_rows,
     const int ee = lane * per_lane + i;
     const int cv = ee < Ne ? cnt[ee] : 0;
     sc += cv;
-    sr += cv > 0;
+    if (RANK) sr += cv > 0;
     st += tile_rows > 0 ? (cv + tile_rows - 1) / tile_rows : 0;
   }
   const int ic = wave_inclusive_scan(sc), it = wave_inclusive_scan(st);
-  const int ir = rk ? wave_inclusive_scan(sr) : 0;
+  const int ir = RANK ? wave_inclusive_scan(sr) : 0;
   int oc = ic - sc, ot = it - st, orr = ir - sr;
   for (int i = 0; i < per_lane; ++i) {
     const int ee = lane * per_lane + i;
@@ -86,30 +87,34 @@ __device__ __forceinline__ void scan_head(const int* cnt, int Ne, int tile_rows,
       const int cv = cnt[ee];
       off[ee] = oc;
       if (ts) ts[ee] = ot;
-      if (rk) rk[ee] = orr;
+      if (RANK) rk[ee] = orr;
       oc += cv;
-      orr += cv > 0;
+      if (RANK) orr += cv > 0;
       ot += tile_rows > 0 ? (cv + tile_rows - 1) / tile_rows : 0;
     }
   }
   if (lane == kWave - 1) {
     off[Ne] = ic;
     if (ts) ts[Ne] = it;
-    if (rk) rk[Ne] = ir;
+    if (RANK) rk[Ne] = ir;
   }
 }
 
 // Grid (ceil(Ne / 64), Nh).  Thread (g, c) of a workgroup handles expert
 // 64 * blockIdx.x + c over the g-th quarter of the token blocks, keeping up
 // to kCachedBlocks of its per-block counts in registers for the prefix pass.
+// RANK: for the weight-stationary FFN's list (0.7 us of 12.8 at 16 x 128 experts
+// where it was a run-time branch; rank_start is no argument for the same reason).
+template <bool RANK>
 __global__ __launch_bounds__(kBucketThreads) void count_scan_kernel(
     const int32_t* __restrict__ partial, int nblk, int Nh, int Ne, int tile_rows,
     int32_t* __restrict__ counts, int32_t* __restrict__ base_rel,
     int32_t* __restrict__ offsets, int32_t* __restrict__ tile_start,
-    int32_t* __restrict__ rank_start, uint32_t* __restrict__ ticket) {
+    uint32_t* __restrict__ ticket) {
   __shared__ int sums[kScanGroups][kScanExperts];
   __shared__ int staged[kStageInts];
   __shared__ bool is_last;
+  int32_t* const rank_start = RANK ? tile_start + (int64_t)Nh * (Ne + 1) : nullptr;
   const int tid = threadIdx.x;
   const int c = tid % kScanExperts, g = tid / kScanExperts;
   const int h = blockIdx.y;
@@ -181,9 +186,9 @@ __global__ __launch_bounds__(kBucketThreads) void count_scan_kernel(
         for (int q = 0; q < kScanGroups; ++q) tot += sums[q][ee];
         staged[ee] = tot;
       }
-      scan_head(staged, Ne, tile_rows, offsets + (int64_t)h * (Ne + 1),
+      scan_head<RANK>(staged, Ne, tile_rows, offsets + (int64_t)h * (Ne + 1),
                 tile_start ? tile_start + (int64_t)h * (Ne + 1) : nullptr,
-                rank_start ? rank_start + (int64_t)h * (Ne + 1) : nullptr);
+                RANK ? rank_start + (int64_t)h * (Ne + 1) : nullptr);
     }
     return;
   }
@@ -220,21 +225,23 @@ __global__ __launch_bounds__(kBucketThreads) void count_scan_kernel(
     }
     __syncthreads();
     for (int hh = wave; hh < nh; hh += kBucketWaves)
-      scan_head(staged + hh * Ne, Ne, tile_rows, offsets + (int64_t)(h0 + hh) * (Ne + 1),
+      scan_head<RANK>(staged + hh * Ne, Ne, tile_rows, offsets + (int64_t)(h0 + hh) * (Ne + 1),
                 tile_start ? tile_start + (int64_t)(h0 + hh) * (Ne + 1) : nullptr,
-                rank_start ? rank_start + (int64_t)(h0 + hh) * (Ne + 1) : nullptr);
+                RANK ? rank_start + (int64_t)(h0 + hh) * (Ne + 1) : nullptr);
     __syncthreads();
   }
   if (tid == 0) *ticket = 0u;
 }
 
 // Grid (token blocks, Nh).  Stable placement of every slot of the block,
-// then this block's share of the head's FFN tile list.
+// then this block's share of the head's FFN tile list (SHARES: and where in it
+// the weight-stationary FFN's workgroups start).
+template <bool SHARES>
 __global__ __launch_bounds__(kBucketThreads) void scatter_kernel(
     const int32_t* __restrict__ idx, const int32_t* __restrict__ base_rel,
     const int32_t* __restrict__ offsets, const int32_t* __restrict__ tile_start,
-    const int32_t* __restrict__ rank_start, int32_t* __restrict__ head_base, int64_t T, int Nh,
-    int Ne, int k, int ebits, int tile_rows, int64_t max_tiles, int32_t* __restrict__ perm,
+    int32_t* __restrict__ head_base, int64_t T, int Nh, int Ne, int k, int ebits,
+    int tile_rows, int64_t max_tiles, int32_t* __restrict__ perm,
     TileInfo* __restrict__ tile_info) {
   __shared__ int whist[kBucketWaves][kMaxExperts];
   __shared__ int s_off[kMaxExperts + 1];
@@ -243,6 +250,7 @@ __global__ __launch_bounds__(kBucketThreads) void scatter_kernel(
   const int blk = blockIdx.x, h = blockIdx.y, nblk = gridDim.x;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int32_t* off_h = offsets + (int64_t)h * (Ne + 1);
+  const int32_t* const rank_start = SHARES ? tile_start + (int64_t)Nh * (Ne + 1) : nullptr;
 
   for (int i = tid; i < kBucketWaves * Ne; i += kBucketThreads)
     whist[i / Ne][i % Ne] = 0;
@@ -260,7 +268,7 @@ __global__ __launch_bounds__(kBucketThreads) void scatter_kernel(
       const int n2 = tile_start[(int64_t)h2 * (Ne + 1) + Ne];
       before += h2 < h ? n2 : 0;
       all += n2;
-      if (rank_start) {
+      if (SHARES) {
         const int r2 = rank_start[(int64_t)h2 * (Ne + 1) + Ne];
         rbefore += h2 < h ? r2 : 0;
         rall += r2;
@@ -270,16 +278,18 @@ __global__ __launch_bounds__(kBucketThreads) void scatter_kernel(
     for (int d = kWave / 2; d > 0; d >>= 1) {
       before += __shfl_xor(before, d, kWave);
       all += __shfl_xor(all, d, kWave);
-      if (rank_start) {
+      if (SHARES) {
         rbefore += __shfl_xor(rbefore, d, kWave);
         rall += __shfl_xor(rall, d, kWave);
       }
     }
     if (lane == 0) {
       s_base = before;
-      s_all = all;
-      s_rank = rbefore;
-      s_rank_all = rall;
+      if (SHARES) {
+        s_all = all;
+        s_rank = rbefore;
+        s_rank_all = rall;
+      }
       if (blk == 0) {
         head_base[h] = before;
         if (h == Nh - 1) head_base[Nh] = all;
@@ -287,7 +297,7 @@ __global__ __launch_bounds__(kBucketThreads) void scatter_kernel(
     }
   }
   __syncthreads();
-  if (rank_start && s_all == 0 && blk == 0 && h == Nh - 1)  // no tile to start the shares
+  if (SHARES && s_all == 0 && blk == 0 && h == Nh - 1)  // no tile to start the shares
     for (int m = tid; m <= kWsGrid; m += kBucketThreads) head_base[Nh + 1 + m] = 0;
   if (T == 0) return;  // (launched only to publish the empty tile list)
 
@@ -362,7 +372,7 @@ __global__ __launch_bounds__(kBucketThreads) void scatter_kernel(
     const int r0 = s_off[lo] + (int)(q - s_ts[lo]) * rpt;
     const int r1 = r0 + rpt < s_off[lo + 1] ? r0 + rpt : s_off[lo + 1];
     tiles_h[q] = TileInfo{lo, r0, r1, h};
-    if (rank_start) {
+    if (SHARES) {
       const int64_t i = s_base + q;
       const WsShares sh = ws_shares_at(i, q == s_ts[lo],
                                        s_rank + rank_start[(int64_t)h * (Ne + 1) + lo] + 1, s_all,
@@ -429,10 +439,14 @@ hipError_t launch_count_scan(const int32_t* partial, int64_t T, int Nh, int Ne,
                              hipStream_t s) {
   const int nblk = (int)num_token_blocks(T);
   const dim3 grid((unsigned)ceil_div(Ne, kScanExperts), (unsigned)Nh);
-  hipLaunchKernelGGL(count_scan_kernel, grid, dim3(kBucketThreads), 0, s, partial,
-                     nblk, Nh, Ne, tile_rows, counts, base_rel, offsets, tile_start,
-                     tile_rows == kWsTileRows ? tile_start + (int64_t)Nh * (Ne + 1) : nullptr,
-                     ticket);
+#define MHL_SCAN(RANK)                                                                        \
+  hipLaunchKernelGGL(count_scan_kernel<RANK>, grid, dim3(kBucketThreads), 0, s, partial, nblk, \
+                     Nh, Ne, tile_rows, counts, base_rel, offsets, tile_start, ticket)
+  if (tile_rows == kWsTileRows)
+    MHL_SCAN(true);
+  else
+    MHL_SCAN(false);
+#undef MHL_SCAN
   return hipGetLastError();
 }
 
@@ -446,10 +460,15 @@ hipError_t launch_scatter(const int32_t* idx, const int32_t* base_rel,
   int ebits = 0;
   while ((1 << ebits) < Ne) ++ebits;
   const dim3 grid(T == 0 ? 1u : (unsigned)num_token_blocks(T), (unsigned)Nh);
-  hipLaunchKernelGGL(scatter_kernel, grid, dim3(kBucketThreads), 0, s, idx,
-                     base_rel, offsets, tile_start,
-                     tile_rows == kWsTileRows ? tile_start + (int64_t)Nh * (Ne + 1) : nullptr,
-                     head_base, T, Nh, Ne, k, ebits, tile_rows, max_tiles, perm, tile_info);
+#define MHL_SCATTER(SHARES)                                                                  \
+  hipLaunchKernelGGL(scatter_kernel<SHARES>, grid, dim3(kBucketThreads), 0, s, idx, base_rel,  \
+                     offsets, tile_start, head_base, T, Nh, Ne, k, ebits, tile_rows, max_tiles, \
+                     perm, tile_info)
+  if (tile_rows == kWsTileRows)
+    MHL_SCATTER(true);
+  else
+    MHL_SCATTER(false);
+#undef MHL_SCATTER
   return hipGetLastError();
 }
 
