@@ -21,14 +21,15 @@
 // step (two sub-steps) hands h over; X rows are gathered by LDS DMA a step
 // ahead.
 //
-// What bounds it: memory.  At 16384 tokens, 16 heads, 256 experts, k 16 a
-// launch gathers 1.07 GB of rows, reads 0.4 GB of weights and writes 1.07 GB of
-// outputs, 5.4 TB/s in the 468 us that it takes.
-// Streaming the weights through LDS instead (ffn_q32_kernel: an expert's
-// weights once per 256 slots, a barrier and a DMA wait per 24 MFMAs) takes
-// 619 us there; a barrier per sub-step with the outputs
-// staged in LDS and stored as whole rows took 8% more than one barrier per
-// step with stores of 64-byte pieces.  (At d_ff 256, with eight wavefronts and
+// What bounds it: memory and issue together.  At 16384 tokens, 16 heads, 256
+// experts, k 16 a launch takes 468 us and moves 2.42 GB by the counters (the
+// gathered rows, 0.4 GB of weights, 1.07 GB of outputs), 5.2 TB/s where the
+// combine's plain read reaches 6; the matrix cores are busy 42% of it, with 9
+// vector operations per MFMA, and no LDS bank conflicts.  Streaming the weights
+// through LDS instead (ffn_q32_kernel: an expert's weights once per 256 slots,
+// a barrier and a DMA wait per 24 MFMAs) takes 619 us there; a barrier per
+// sub-step with the outputs staged in LDS and stored as whole rows took 8% more
+// than one barrier per step with stores of 64-byte pieces.  (At d_ff 256, with eight wavefronts and
 // 16-row GEMM2 tiles, the same scheme measured no better than ffn_q32_kernel,
 // which stays there.)
 #include <math.h>
