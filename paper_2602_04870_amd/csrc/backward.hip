@@ -968,9 +968,8 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t row_buffer(const uint16_t* row
                                            0x00020000);
 }
 
-// GLOBAL (CPW == 2): rows by global LDS DMA instead of through buffers (see
-// bwd_dw_form).
-template <bool GELU, int CPW, bool GLOBAL>
+// FAR (CPW == 2): X and dY reach past a 4 GiB buffer (see bwd_dw_form).
+template <bool GELU, int CPW, bool FAR = false>
 __global__ __launch_bounds__(kBwdThreads * CPW, CPW == 1 ? 2 : 1) void bwd_dw2_kernel(
     const uint16_t* __restrict__ X, const uint16_t* __restrict__ dY,
     const float* __restrict__ gate,
@@ -1030,13 +1029,11 @@ __global__ __launch_bounds__(kBwdThreads * CPW, CPW == 1 ? 2 : 1) void bwd_dw2_k
   // DMA form: rows of instruction i of wavefront w are tile rows RPW w + 4 i
   // + [0, 4), 1 KiB of LDS at a uniform base, lane l's 16 bytes at 16 l
   // (row l / 16, physical unit l % 16): the layout the register path stores.
-  // (Buffer rather than global LDS DMA: the compiler takes the latter for a
-  // flat access that also counts as an LDS operation, and turns every wait for
-  // a fragment into lgkmcnt(0), the reads two K steps ahead included.  Either
-  // is tracked, so phase B's first transposing read waits for vmcnt(0), these
-  // rows included; with dma_lds16, which avoids that, the kernel was slower all
-  // the same: layer backward 374.5 -> 378 us at 4096 tokens / 64 experts, the
-  // skewed training step 17.09 -> 17.17 ms, the 384-expert GELU one 949 -> 953.)
+  // (Buffer and not global LDS DMA where the buffers reach: the compiler takes
+  // the latter for a flat access that also counts as an LDS operation, and
+  // turned every wait for a fragment into lgkmcnt(0), the reads two K steps
+  // ahead included.  Either is tracked, so phase B's first transposing read
+  // waits for vmcnt(0), these rows included, as dma_lds16 describes.)
   const __amdgpu_buffer_rsrc_t xrs = row_buffer(X, T * Nh * (DH * 2));
   const __amdgpu_buffer_rsrc_t yrs = row_buffer(dY, T * Nh * (DH * 2));
   auto fetch_dma = [&](const int* sl4, int buf) {
@@ -1050,7 +1047,7 @@ __global__ __launch_bounds__(kBwdThreads * CPW, CPW == 1 ? 2 : 1) void bwd_dw2_k
       const int64_t th = t * Nh + h;
       const int u = swz_tr<L::NJ1>(pu, r);
       uint8_t* dst = smem + S::X_OFF + buf * S::RBUF + (RPW * wave + 4 * i) * S::TROW;
-      if constexpr (GLOBAL) {
+      if constexpr (FAR) {
         __builtin_amdgcn_global_load_lds(
             X + th * DH + 8 * u, (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
         __builtin_amdgcn_global_load_lds(
@@ -1590,18 +1587,18 @@ hipError_t launch_bwd_dw(const void* X, const void* dY, const float* gate,
   hipLaunchKernelGGL((bwd_dw_kernel<DH, G>), grid, dim3(kBwdThreads), 0, s, (const uint16_t*)X, \
                      (const uint16_t*)dY, gate, perm, offsets, order, (const uint16_t*)W1, w3,  \
                      (const uint16_t*)W2, T, Nh, Ne, k, dff, dW1, dW3, dW2)
-  const DwForm form = bwd_dw_form(T, Nh, dff, gelu);
+  const DwForm form = bwd_dw_form(T, Nh, dff);
   const int cpw = form == DwForm::kOneChunk ? 1 : 2;
   const dim3 grid2((unsigned)(pairs8 * (dff / kChunk / cpw)));
-#define MHL_BWD_DW2(G, C, GLOBAL)                                                              \
-  hipLaunchKernelGGL((bwd_dw2_kernel<G, C, GLOBAL>), grid2, dim3(kBwdThreads * C), 0, s,      \
+#define MHL_BWD_DW2(G, C, FAR)                                                                 \
+  hipLaunchKernelGGL((bwd_dw2_kernel<G, C, FAR>), grid2, dim3(kBwdThreads * C), 0, s,         \
                      (const uint16_t*)X, (const uint16_t*)dY, gate, perm, offsets, order,       \
                      (const uint16_t*)W1, w3, (const uint16_t*)W2, T, Nh, Ne, k, dff, dW1, dW3, dW2)
-#define MHL_BWD_DW2_FORM(G)                                               \
-  do {                                                                    \
-    if (form == DwForm::kOneChunk) MHL_BWD_DW2(G, 1, false);              \
-    else if (form == DwForm::kTwoChunksBuffer) MHL_BWD_DW2(G, 2, false);  \
-    else MHL_BWD_DW2(G, 2, true);                                         \
+#define MHL_BWD_DW2_FORM(G)                                  \
+  do {                                                       \
+    if (form == DwForm::kOneChunk) MHL_BWD_DW2(G, 1, false); \
+    else if (form == DwForm::kTwoChunks) MHL_BWD_DW2(G, 2, false); \
+    else MHL_BWD_DW2(G, 2, true);                            \
   } while (0)
   if (dh == 128 && !gelu)
     MHL_BWD_DW2_FORM(false);

@@ -238,21 +238,13 @@ hipError_t launch_dw_plan(const int32_t* offsets, int Nh, int Ne, int32_t* order
 
 // The weight-gradient kernel's form at d_h 128: an even number of 32-wide d_ff
 // chunks goes two per workgroup (8 wavefronts share the gathered slot rows),
-// else one.  The two-chunk form reads the rows through 4 GiB buffers, or by
-// global LDS DMA with 64-bit addresses in batches past them (2^24 rows, k 2, 64
-// experts, d_ff 128 / 256: 10.4 / 19.2 ms that way, 12.2 / 22.3 ms one chunk per
-// workgroup) and for a single head's SwiGLU experts.  There a hot expert's rows
-// are nearly all of the batch's, one after another, and one workgroup's chain of
-// them is the launch: buffer 1854 us, global 1806 (62920 tokens, 78 experts, k
-// 6, Zipf), 1981 / 1942 (65536, 128, k 8, d_ff 512); at an even load the two are
-// level.  With two heads and more they are level on hot experts and the buffer
-// is 0 to 1.5% faster on even loads, and the GELU expert is 3 to 4% faster with
-// it everywhere.
-enum class DwForm { kOneChunk, kTwoChunksBuffer, kTwoChunksGlobal };
-inline DwForm bwd_dw_form(int64_t T, int Nh, int dff, bool gelu) {
+// else one.  The two-chunk form reads the rows through 4 GiB buffers; batches
+// past them take 64-bit row addresses (2^24 rows, k 2, 64 experts, d_ff 128 /
+// 256: 10.4 / 19.2 ms that way, 12.2 / 22.3 ms one chunk per workgroup).
+enum class DwForm { kOneChunk, kTwoChunks, kTwoChunksFar };
+inline DwForm bwd_dw_form(int64_t T, int Nh, int dff) {
   if ((dff / 32) % 2 != 0) return DwForm::kOneChunk;
-  if (T * Nh >= (int64_t(1) << 24) || (Nh == 1 && !gelu)) return DwForm::kTwoChunksGlobal;
-  return DwForm::kTwoChunksBuffer;
+  return T * Nh < (int64_t(1) << 24) ? DwForm::kTwoChunks : DwForm::kTwoChunksFar;
 }
 
 // Backward, step 3: dW1, dW3 and dW2 of every (head, expert), written in

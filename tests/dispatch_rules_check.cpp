@@ -54,14 +54,12 @@ void check_shares(const char* what, const std::vector<int64_t>& counts, int sw) 
 }  // namespace
 
 int main() {
-  // dw T Nh dff gelu form: the weight-gradient kernel's form at d_h 128
+  // dw T Nh dff form: the weight-gradient kernel's form at d_h 128
   for (int dff = 32; dff <= 512; dff += 32)
     for (const int Nh : {1, 3, 8})
       for (const int64_t T : {int64_t(0), int64_t(1), int64_t(4096), (int64_t(1) << 24) / Nh - 1,
                               (int64_t(1) << 24) / Nh, (int64_t(1) << 24) / Nh + 1, int64_t(1) << 27})
-        for (const bool gelu : {false, true})
-          std::printf("dw %lld %d %d %d %d\n", (long long)T, Nh, dff, gelu,
-                      (int)bwd_dw_form(T, Nh, dff, gelu));
+        std::printf("dw %lld %d %d %d\n", (long long)T, Nh, dff, (int)bwd_dw_form(T, Nh, dff));
   for (const int sw : {0, 2}) {
     check_shares("one_slot", {0, 0, 1, 0}, sw);
     check_shares("one_expert", {0, 70000, 0}, sw);

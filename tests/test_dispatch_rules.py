@@ -29,18 +29,15 @@ def lines(tmp_path_factory):
 
 def test_weight_gradients_take_two_chunks_at_every_batch(lines):
     """An even number of d_ff chunks goes two per workgroup whatever the batch;
-    past a 4 GiB row buffer, and for a single head's SwiGLU experts, by 64-bit
-    addresses."""
+    past a 4 GiB row buffer by 64-bit addresses."""
     rows = [[int(v) for v in ln[1:]] for ln in lines if ln[0] == "dw"]
-    assert len(rows) == 16 * 3 * 7 * 2
-    one, two_buffer, two_global = 0, 1, 2
-    for T, Nh, dff, gelu, form in rows:
+    assert len(rows) == 16 * 3 * 7
+    one, two, two_far = 0, 1, 2
+    for T, Nh, dff, form in rows:
         if dff % 64:
             assert form == one
-        elif T * Nh * 256 >= 1 << 32 or (Nh == 1 and not gelu):
-            assert form == two_global
         else:
-            assert form == two_buffer
+            assert form == (two if T * Nh * 256 < 1 << 32 else two_far)
 
 
 def test_stationary_ffn_shares_are_equal_in_cost(lines):
