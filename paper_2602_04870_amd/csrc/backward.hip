@@ -1033,7 +1033,10 @@ __global__ __launch_bounds__(kBwdThreads * CPW, CPW == 1 ? 2 : 1) void bwd_dw2_k
   // the latter for a flat access that also counts as an LDS operation, and
   // turned every wait for a fragment into lgkmcnt(0), the reads two K steps
   // ahead included.  Either is tracked, so phase B's first transposing read
-  // waits for vmcnt(0), these rows included, as dma_lds16 describes.)
+  // waits for vmcnt(0), these rows included; with dma_lds16, which avoids that,
+  // the kernel was slower all the same: layer backward 374.5 -> 378 us at 4096
+  // tokens / 64 experts, the skewed training step 17.09 -> 17.17 ms, the
+  // 384-expert GELU one 949 -> 953 us.)
   const __amdgpu_buffer_rsrc_t xrs = row_buffer(X, T * Nh * (DH * 2));
   const __amdgpu_buffer_rsrc_t yrs = row_buffer(dY, T * Nh * (DH * 2));
   auto fetch_dma = [&](const int* sl4, int buf) {
@@ -1046,6 +1049,11 @@ __global__ __launch_bounds__(kBwdThreads * CPW, CPW == 1 ? 2 : 1) void bwd_dw2_k
       const int j = sl - (int)t * k;
       const int64_t th = t * Nh + h;
       const int u = swz_tr<L::NJ1>(pu, r);
+      // (src before dst: the other way round the compiler sets m0 between the
+      // address and the load, 3% of the kernel where one workgroup's chain of a
+      // hot expert's slots is the launch: 537 -> 556 us at 17920 tokens, 2 heads,
+      // 13 experts, k 8, d_ff 384, Zipf load.)
+      const uint32_t src = (uint32_t)th * (DH * 2) + 16 * u;
       uint8_t* dst = smem + S::X_OFF + buf * S::RBUF + (RPW * wave + 4 * i) * S::TROW;
       if constexpr (FAR) {
         __builtin_amdgcn_global_load_lds(
@@ -1054,7 +1062,6 @@ __global__ __launch_bounds__(kBwdThreads * CPW, CPW == 1 ? 2 : 1) void bwd_dw2_k
             dY + th * DH + 8 * u, (__attribute__((address_space(3))) void*)(dst + S::TILE), 16, 0,
             0);
       } else {
-        const uint32_t src = (uint32_t)th * (DH * 2) + 16 * u;
         __builtin_amdgcn_raw_ptr_buffer_load_lds(
             xrs, (__attribute__((address_space(3))) void*)dst, 16, src, 0, 0, 0);
         __builtin_amdgcn_raw_ptr_buffer_load_lds(
