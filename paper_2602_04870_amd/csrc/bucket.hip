@@ -355,7 +355,10 @@ __global__ __launch_bounds__(kBucketThreads) void scatter_kernel(
   if (tile_info == nullptr) return;
   const int nt = s_ts[Ne];
   TileInfo* tiles_h = tile_info + s_base;
-  const int64_t chunk = ceil_div(max_tiles, nblk);
+  // At least a tile per thread, so that the blocks that start last have none to
+  // write (7.6 -> 6.9 us at 4096 tokens, 8 heads, k 8 against equal shares).
+  int64_t chunk = ceil_div(max_tiles, nblk);
+  if (chunk < kBucketThreads) chunk = kBucketThreads;
   const int64_t q_end = (blk + 1) * chunk < nt ? (blk + 1) * chunk : nt;
   for (int64_t q = blk * chunk + tid; q < q_end; q += kBucketThreads) {
     // expert e with s_ts[e] <= q < s_ts[e + 1]
